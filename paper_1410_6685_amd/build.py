@@ -17,7 +17,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(os.path.dirname(HERE), "_build")
 LIB = os.path.join(HERE, "libsafegpu.so")
 SOURCES = ["stream.hip", "gemm.hip", "product.hip", "runtime.hip", "planner.hip", "exec.hip", "batch.hip", "mlp.hip", "tune.hip",
-           "jit.hip", "host_checks.hip", "qsort.hip", "nodes.hip", "gauss.hip", "linalg.hip",
+           "jit.hip", "host_checks.hip", "qsort.hip", "radix.hip", "nodes.hip", "gauss.hip", "linalg.hip",
            "persist.hip", "expr.hip", "noalloc.hip"]
 # kernel sources compiled again at run time (hiprtc) for specialized passes; embedded in the
 # library as strings

@@ -100,6 +100,37 @@ def test_quicksort_large_against_stable_sort(sg, ctx, n, kind):
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("n,lo,hi,offset", [
+    (2049, -2**31, 2**31 - 1, 0),               # the smallest digit sort, one chunk with a ragged tile
+    (6144, 100, 100, 1),                        # one key: a single pass; unaligned input
+    (70_001, -128, 127, 3),                     # one digit
+    (70_001, 2**31 - 60_000, 2**31 - 1, 0),     # two digits at the top of the range
+    (300_007, -(2**23), 2**23, 2),              # four digits (the range's ends straddle 2^24)
+    (300_007, 0, 2**24 - 257, 0),               # three digits
+    (256 * 512 * 16 - 1, -5, 2**20, 1),         # last size of the small tiles
+    (256 * 512 * 16, -2**31, 2**31 - 1, 0),     # first size of the large ones
+    (256 * 512 * 16 + 8191, -2**31, 2**31 - 1, 1),
+    (20_000_003, -2**31, -2**31 + 999, 0)])     # several tiles per chunk, many ties
+def test_digit_sort_edges(sg, ctx, n, lo, hi, offset):
+    """Tile and chunk edges, every number of digit passes and unaligned inputs of the digit sort,
+    as int32 and as float32 (both zeros among the items), against numpy's stable sort."""
+    import torch
+    say("digit sort", n, lo, hi, offset)
+    x = W.uniform_i32(n, 9, lo, hi)
+    f = x.astype(np.float32)
+    f[::5] = 0.0
+    f[1::5] = -0.0
+    f[2::7] = np.inf
+    for a in (x, f):
+        host = np.concatenate([a[:offset], a])
+        dev = torch.from_numpy(host).cuda()[offset:]
+        built = sg.build_spec(ctx, qs_spec(n, "i32" if a is x else "f32"), {"a": dev})
+        status, verdicts = built.program.execute()
+        assert status == "ok" and [(v.holds, v.first_index) for v in verdicts] == [(1, -1), (1, -1)]
+        got = built["r"].to_host("i32" if a is x else "f32")
+        assert np.array_equal(got.view(np.uint32), np.sort(a, kind="stable").view(np.uint32))
+
+
 def test_concat_and_item(sg, ctx):
     n = 50_000
     x, y = W.normal_f32(n, 1), W.normal_f32(n // 3, 2)
