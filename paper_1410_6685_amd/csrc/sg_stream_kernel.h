@@ -273,6 +273,146 @@ __device__ __forceinline__ uint64_t tag_word(uint32_t epoch, uint32_t payload) {
     return ((uint64_t)epoch << 32) | payload;
 }
 
+// Combine a block's exact accumulators of instance `cur` and publish its buffered tiles; the
+// block holding the instance's last tile finalizes.  acc_take(k) and sum_take(k) give a lane's
+// accumulators and reset them.
+template <bool INLINE, class LDS, class AccTake, class SumTake>
+__device__ __forceinline__ void flush_instance(const StreamArgs& A, LDS& L, kptr kdesc, const char* D, int cur,
+                                               int64_t tile0, int64_t ntiles, int ns, int nsum, int& ntl,
+                                               uint32_t epoch, uint32_t wlimit, AccTake&& acc_take, SumTake&& sum_take) {
+    const int tid = threadIdx.x, lane = tid & 63, B = blockDim.x, nwaves = B >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int spread = A.spread, sp_idx = (int)(blockIdx.x % (unsigned)spread);
+    // single program: the block's sums, over lanes then waves in a fixed order
+    if (INLINE) {
+        for (int k = 0; k < nsum; ++k) {
+            double s = sum_take(k);
+            s = wave_sum_f64(s);
+            if (lane == 0) L.sum[wave][k] = s;
+        }
+    }
+    for (int k = 0; k < ns; ++k) {
+        const uint8_t kind = d8_lane<INLINE>(kdesc, D, (int)__builtin_offsetof(InstDesc, slot_kind) + k);
+        uint64_t v = acc_take(k);
+        v = kind == SLOT_ADD ? (uint64_t)wave_sum_i64((int64_t)v) : wave_max_u64(v);
+        if (lane == 0) L.slot[wave][k] = v;
+    }
+    __syncthreads();
+    if (INLINE && tid < nsum) {
+        double s = 0.0;
+        for (int w = 0; w < nwaves; ++w) s += L.sum[w][tid];
+        L.tsum[0][tid] = s;
+    }
+    if (tid < ns) {
+        const uint8_t kind = d8_lane<INLINE>(kdesc, D, (int)__builtin_offsetof(InstDesc, slot_kind) + tid);
+        uint64_t v = 0;
+        for (int w = 0; w < nwaves; ++w) {
+            const uint64_t x = L.slot[w][tid];
+            v = kind == SLOT_ADD ? v + x : (x > v ? x : v);
+        }
+        uint64_t* g = A.acc + ((int64_t)cur * MAX_SLOTS + tid) * spread + sp_idx;
+        if (v) {
+            if (kind == SLOT_ADD) (void)__hip_atomic_fetch_add(g, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else (void)__hip_atomic_fetch_max(g, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0);  // accumulator updates complete before the tiles are published
+    __syncthreads();
+    // a single program publishes one running sum per block (its tiles in order), indexed
+    // by block; a batched launch one word set per buffered tile
+    bool has_last = false;
+    if (INLINE) {
+        has_last = (int64_t)blockIdx.x == (ntiles - 1) % (int64_t)gridDim.x;
+    } else {
+        for (int q = 0; q < ntl; ++q) has_last |= L.tile[q] == tile0 + ntiles - 1;
+    }
+    const int words = 1 + 2 * nsum;
+    for (int idx = tid; idx < ntl * words; idx += B) {
+        const int q = idx / words, w = idx % words;
+        uint32_t payload = 0;
+        if (w > 0) {
+            const uint64_t bits = __builtin_bit_cast(uint64_t, L.tsum[q][(w - 1) >> 1]);
+            payload = ((w - 1) & 1) ? (uint32_t)(bits >> 32) : (uint32_t)bits;  // low half first
+        }
+        const int64_t where = INLINE ? (int64_t)blockIdx.x : L.tile[q];
+        __hip_atomic_store(&A.tags[where * TAG_WORDS + w], tag_word(epoch, payload), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    ntl = 0;
+    if (!has_last) return;
+    // ---- finalize the instance ----
+    // Everything read here was written by other blocks, past this XCD's L2: a round trip per
+    // dependent load.  Four words per thread are in flight at a time, and a slot's copies lie
+    // across the lanes of a wave (read one after another by one thread they took 8 us of a 37 us
+    // execution over 1000 elements, and 20 of the 265 us of the 2^26 filter pass).
+    InstResult* res = A.results + cur;
+    // word sets to wait for: one per block (single program; every block holds a tile) or
+    // one per tile of the instance
+    const int64_t nq = INLINE ? (int64_t)gridDim.x : ntiles;
+    const int64_t q0 = INLINE ? 0 : tile0;
+    for (uint32_t spins = 0;; ++spins) {
+        if (spins >= wlimit) {  // bounded: report instead of hanging
+            if (tid == 0) atomicOr(&res->err, (uint32_t)ERR_FINALIZE_TIMEOUT);
+            break;
+        }
+        int ok = 1;
+        for (int w = 0; w < words; ++w)
+            for (int64_t q = tid; q < nq; q += 4 * B) {
+                uint64_t x[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    x[j] = q + j * B < nq ? ld_relaxed(&A.tags[(q0 + q + j * B) * TAG_WORDS + w]) : tag_word(epoch, 0);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) ok &= (uint32_t)(x[j] >> 32) == epoch;
+            }
+        if (__syncthreads_and(ok)) break;
+        __builtin_amdgcn_s_sleep(2);
+    }
+    for (int k = 0; k < nsum; ++k) {
+        double s = 0.0;
+        for (int64_t q = tid; q < nq; q += 4 * B) {
+            uint64_t lo[4], hi[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint64_t* tw = A.tags + (q0 + q + j * B) * TAG_WORDS + 1 + 2 * k;
+                lo[j] = q + j * B < nq ? ld_relaxed(tw) : 0;
+                hi[j] = q + j * B < nq ? ld_relaxed(tw + 1) : 0;
+            }
+            // in the order of the blocks (or tiles)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (q + j * B < nq)
+                    s += __builtin_bit_cast(double, ((hi[j] & 0xFFFFFFFFull) << 32) | (lo[j] & 0xFFFFFFFFull));
+        }
+        s = wave_sum_f64(s);
+        if (lane == 0) L.fin[wave][k] = s;
+    }
+    __syncthreads();
+    if (tid < nsum) {
+        double s = 0.0;
+        for (int w = 0; w < nwaves; ++w) s += L.fin[w][tid];
+        res->sum[tid] = s;
+    }
+    const int count_slot = (int)d32<INLINE>(kdesc, D, (int)__builtin_offsetof(InstDesc, count_slot));
+    for (int k = wave; k < ns; k += nwaves) {  // exact sums and maxima: any order
+        const uint8_t kind = d8_lane<INLINE>(kdesc, D, (int)__builtin_offsetof(InstDesc, slot_kind) + k);
+        uint64_t v = 0;
+        uint64_t* g = A.acc + ((int64_t)cur * MAX_SLOTS + k) * spread;
+        for (int j = lane; j < spread; j += 64) {
+            const uint64_t x = ld_relaxed(g + j);
+            v = kind == SLOT_ADD ? v + x : (x > v ? x : v);
+            if (x) st_relaxed(g + j, 0);
+        }
+        v = kind == SLOT_ADD ? (uint64_t)wave_sum_i64((int64_t)v) : wave_max_u64(v);
+        if (lane == 0) {
+            res->slot[k] = (int64_t)v;
+            if (k == count_slot) res->scan_count = (int64_t)v;
+        }
+    }
+    __syncthreads();
+}
+
 // ---- the kernel ----------------------------------------------------------------------------
 //
 // A tile is `substeps` consecutive sub-tiles of blockDim.x * 4U elements of one instance.
@@ -335,8 +475,6 @@ __global__ __launch_bounds__(LB, LB <= 256 ? 2 : 1) void stream_kernel(const Str
         ? __builtin_amdgcn_readfirstlane(__hip_atomic_load(A.limit_ptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
         : A.wait_limit;
     const uint32_t wlimit = wraw == 0 ? kDefaultWaitSpins : wraw - 1u;
-    const int spread = A.spread;
-    const int sp_idx = (int)(blockIdx.x % (unsigned)spread);
     const kptr kargs = (kptr)__builtin_amdgcn_kernarg_segment_ptr();
     const kptr kdesc = kargs + __builtin_offsetof(StreamArgs, inst0);
     const kptr kprog = kargs + __builtin_offsetof(StreamArgs, prog0);
@@ -420,119 +558,8 @@ __global__ __launch_bounds__(LB, LB <= 256 ? 2 : 1) void stream_kernel(const Str
     for (int i = tid; i < (1 << SG_EXPF_BITS); i += blockDim.x) L.exptab[i] = SG_EXPF_TAB[i];
     lds_barrier();
 
-    // Combine the block's exact accumulators of instance `cur`, publish its buffered tiles;
-    // the block holding the instance's last tile finalizes.
     auto flush = [&]() {
-        // single program: the block's sums, over lanes then waves in a fixed order
-        if (INLINE) {
-            for (int k = 0; k < nsum; ++k) {
-                double s = sum_take(k);
-                s = wave_sum_f64(s);
-                if (lane == 0) L.sum[wave][k] = s;
-            }
-        }
-        for (int k = 0; k < ns; ++k) {
-            const uint8_t kind = d8_lane<INLINE>(kdesc, D, (int)__builtin_offsetof(InstDesc, slot_kind) + k);
-            uint64_t v = acc_take(k);
-            v = kind == SLOT_ADD ? (uint64_t)wave_sum_i64((int64_t)v) : wave_max_u64(v);
-            if (lane == 0) L.slot[wave][k] = v;
-        }
-        __syncthreads();
-        if (INLINE && tid < nsum) {
-            double s = 0.0;
-            for (int w = 0; w < nwaves; ++w) s += L.sum[w][tid];
-            L.tsum[0][tid] = s;
-        }
-        if (tid < ns) {
-            const uint8_t kind = d8_lane<INLINE>(kdesc, D, (int)__builtin_offsetof(InstDesc, slot_kind) + tid);
-            uint64_t v = 0;
-            for (int w = 0; w < nwaves; ++w) {
-                const uint64_t x = L.slot[w][tid];
-                v = kind == SLOT_ADD ? v + x : (x > v ? x : v);
-            }
-            uint64_t* g = A.acc + ((int64_t)cur * MAX_SLOTS + tid) * spread + sp_idx;
-            if (v) {
-                if (kind == SLOT_ADD) (void)__hip_atomic_fetch_add(g, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                else (void)__hip_atomic_fetch_max(g, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-        __builtin_amdgcn_s_waitcnt(0);  // accumulator updates complete before the tiles are published
-        __syncthreads();
-        // a single program publishes one running sum per block (its tiles in order), indexed
-        // by block; a batched launch one word set per buffered tile
-        bool has_last = false;
-        if (INLINE) {
-            has_last = (int64_t)blockIdx.x == (ntiles - 1) % (int64_t)gridDim.x;
-        } else {
-            for (int q = 0; q < ntl; ++q) has_last |= L.tile[q] == tile0 + ntiles - 1;
-        }
-        const int words = 1 + 2 * nsum;
-        for (int idx = tid; idx < ntl * words; idx += B) {
-            const int q = idx / words, w = idx % words;
-            uint32_t payload = 0;
-            if (w > 0) {
-                const uint64_t bits = __builtin_bit_cast(uint64_t, L.tsum[q][(w - 1) >> 1]);
-                payload = ((w - 1) & 1) ? (uint32_t)(bits >> 32) : (uint32_t)bits;  // low half first
-            }
-            const int64_t where = INLINE ? (int64_t)blockIdx.x : L.tile[q];
-            __hip_atomic_store(&A.tags[where * TAG_WORDS + w], tag_word(epoch, payload), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __syncthreads();
-        ntl = 0;
-        if (!has_last) return;
-        // ---- finalize the instance ----
-        InstResult* res = A.results + cur;
-        // word sets to wait for: one per block (single program; every block holds a tile) or
-        // one per tile of the instance
-        const int64_t nq = INLINE ? (int64_t)gridDim.x : ntiles;
-        const int64_t q0 = INLINE ? 0 : tile0;
-        for (uint32_t spins = 0;; ++spins) {
-            if (spins >= wlimit) {  // bounded: report instead of hanging
-                if (tid == 0) atomicOr(&res->err, (uint32_t)ERR_FINALIZE_TIMEOUT);
-                break;
-            }
-            int ok = 1;
-            for (int64_t q = tid; q < nq; q += B)
-                for (int w = 0; w < words; ++w) {
-                    const uint64_t x = __hip_atomic_load(&A.tags[(q0 + q) * TAG_WORDS + w], __ATOMIC_RELAXED,
-                                                         __HIP_MEMORY_SCOPE_AGENT);
-                    ok &= (uint32_t)(x >> 32) == epoch;
-                }
-            if (__syncthreads_and(ok)) break;
-            __builtin_amdgcn_s_sleep(2);
-        }
-        for (int k = 0; k < nsum; ++k) {
-            double s = 0.0;
-            for (int64_t q = tid; q < nq; q += B) {
-                const uint64_t* tw = A.tags + (q0 + q) * TAG_WORDS + 1 + 2 * k;
-                const uint64_t lo = __hip_atomic_load(tw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const uint64_t hi = __hip_atomic_load(tw + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                s += __builtin_bit_cast(double, ((hi & 0xFFFFFFFFull) << 32) | (lo & 0xFFFFFFFFull));
-            }
-            s = wave_sum_f64(s);
-            if (lane == 0) L.fin[wave][k] = s;
-        }
-        __syncthreads();
-        if (tid < nsum) {
-            double s = 0.0;
-            for (int w = 0; w < nwaves; ++w) s += L.fin[w][tid];
-            res->sum[tid] = s;
-        }
-        const int count_slot = (int)d32<INLINE>(kdesc, D, (int)__builtin_offsetof(InstDesc, count_slot));
-        if (tid < ns) {
-            const uint8_t kind = d8_lane<INLINE>(kdesc, D, (int)__builtin_offsetof(InstDesc, slot_kind) + tid);
-            uint64_t v = 0;
-            uint64_t* g = A.acc + ((int64_t)cur * MAX_SLOTS + tid) * spread;
-            for (int j = 0; j < spread; ++j) {
-                const uint64_t x = __hip_atomic_load(g + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                v = kind == SLOT_ADD ? v + x : (x > v ? x : v);
-                if (x) __hip_atomic_store(g + j, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            res->slot[tid] = (int64_t)v;
-            if (tid == count_slot) res->scan_count = (int64_t)v;
-        }
-        __syncthreads();
+        flush_instance<INLINE>(A, L, kdesc, D, cur, tile0, ntiles, ns, nsum, ntl, epoch, wlimit, acc_take, sum_take);
     };
 
     // ---- compaction state ----
