@@ -18,7 +18,7 @@
 using namespace sg;
 using namespace sgrt;
 
-hipError_t sg_launch_stream(const StreamArgs& a, int unroll, bool inl, int grid, int block, size_t lds_bytes,
+hipError_t sg_launch_stream(const StreamArgs& a, int unroll, bool inl, bool lean, int grid, int block, size_t lds_bytes,
                             hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 hipError_t sg_launch_epoch_bump(uint32_t* e, hipStream_t s);
 hipError_t sg_launch_set_word(uint32_t* p, uint32_t v, hipStream_t s);
@@ -32,6 +32,7 @@ struct sg_batch_s {
     StreamArgs args;
     int grid = 1, block = 256, unroll = 2, substeps = 1;
     size_t lds = 0;
+    bool lean = false;               // every program runs on the lean interpreter
     int64_t total_tiles = 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -85,7 +86,11 @@ sg_status sg_batch_create(sg_ctx ctx, const sg_program* progs, int32_t n, int us
         max_sums = std::max(max_sums, ip.nsum);
         max_cemit = std::max(max_cemit, inst_cemit(ip));
         any_scan |= ip.scan_space != 0;
+        ip.lean = lean_program(ip);
+        b->lean = (i == 0 || b->lean) && !ip.lean.empty();
     }
+    b->lean &= b->block <= LEAN_BLOCK;
+    if (b->lean) max_sums = 0;  // the lean kernel keeps its sums in registers
     // the per-lane accumulators and staging buffers of every instance must fit in LDS
     for (;; b->unroll /= 2) {
         b->substeps = stream_substeps(ctx->batch_substeps, b->block, b->unroll, max_slots, max_sums, max_cemit,
@@ -102,9 +107,11 @@ sg_status sg_batch_create(sg_ctx ctx, const sg_program* progs, int32_t n, int us
         InstPlan& ip = b->progs[i]->plan.insts[0];
         const int64_t nt = std::max<int64_t>(1, (ip.n + tile_elems - 1) / tile_elems);
         InstDesc d;
+        const std::vector<SgOp>& prog = b->lean ? ip.lean : ip.prog;
         fill_inst(ip, d, b->total_tiles, nt, (int)ops.size());
+        if (b->lean) set_lean(d, prog);
         descs.push_back(d);
-        ops.insert(ops.end(), ip.prog.begin(), ip.prog.end());
+        ops.insert(ops.end(), prog.begin(), prog.end());
         for (int64_t t = 0; t < nt; ++t) tile_inst.push_back(i);
         b->total_tiles += nt;
     }
@@ -142,7 +149,7 @@ sg_status sg_batch_create(sg_ctx ctx, const sg_program* progs, int32_t n, int us
     a.lds_slots = max_slots;
     a.lds_sums = max_sums;
     a.lds_cemit = max_cemit;
-    b->grid = stream_grid(ctx, b->total_tiles, false, b->unroll, b->block, b->lds, any_scan);
+    b->grid = stream_grid(ctx, b->total_tiles, false, b->lean, b->unroll, b->block, b->lds, any_scan);
     if (hipStreamSynchronize(ctx->stream) != hipSuccess) { batch_free(b); return fail(ctx, SG_E_DEVICE, "batch sync"); }
     if (use_graph) {
         // the graph holds only the kernel node (no memset nodes): the kernel leaves its
@@ -155,7 +162,7 @@ sg_status sg_batch_create(sg_ctx ctx, const sg_program* progs, int32_t n, int us
         }
         hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
         if (e == hipSuccess) e = sg_launch_epoch_bump(b->scratch.epoch, cs);
-        if (e == hipSuccess) e = sg_launch_stream(a, b->unroll, false, b->grid, b->block, b->lds, cs);
+        if (e == hipSuccess) e = sg_launch_stream(a, b->unroll, false, b->lean, b->grid, b->block, b->lds, cs);
         hipError_t e2 = hipStreamEndCapture(cs, &b->graph);
         if (own) (void)hipStreamDestroy(cs);
         if (e != hipSuccess || e2 != hipSuccess) { batch_free(b); return fail(ctx, SG_E_DEVICE, "graph capture failed"); }
@@ -179,7 +186,7 @@ sg_status sg_batch_launch(sg_batch b) {
         SG_HIP(ctx, hipGraphLaunch(b->exec, ctx->stream));
     } else {
         SG_HIP(ctx, sg_launch_epoch_bump(b->scratch.epoch, ctx->stream));
-        SG_HIP(ctx, sg_launch_stream(b->args, b->unroll, false, b->grid, b->block, b->lds, ctx->stream));
+        SG_HIP(ctx, sg_launch_stream(b->args, b->unroll, false, b->lean, b->grid, b->block, b->lds, ctx->stream));
     }
     return SG_OK;
 }

@@ -20,14 +20,14 @@
 
 using namespace sg;
 
-hipError_t sg_launch_stream(const StreamArgs& a, int unroll, bool inl, int grid, int block, size_t lds_bytes,
+hipError_t sg_launch_stream(const StreamArgs& a, int unroll, bool inl, bool lean, int grid, int block, size_t lds_bytes,
                             hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 hipError_t sg_launch_gemm_f32(const float* A, const float* B, float* C, int64_t M, int64_t N, int64_t K, hipStream_t s);
 hipError_t sg_launch_product_check(const float* C, const float* A, const float* B, const float* R, int64_t M,
                                    int64_t N, int64_t K, int64_t nvec, double tol, double* work, InstResult* res,
                                    hipStream_t s);
 size_t sg_product_check_work_bytes(int64_t M, int64_t N, int64_t K);
-int sg_stream_occupancy(int unroll, bool inl, int block, size_t lds_bytes);
+int sg_stream_occupancy(int unroll, bool inl, bool lean, int block, size_t lds_bytes);
 hipError_t sg_launch_zero(uint64_t* p, int64_t n, hipStream_t s);
 
 namespace sgrt {
@@ -65,18 +65,71 @@ int coresident_blocks(int occupancy, int lds_blocks, bool waits_on_others) {
     return std::max(occ >= 3 ? occ - 1 : occ, 1);
 }
 
-int stream_grid(sg_ctx_s* ctx, int64_t ntiles, bool inl, int unroll, int block, size_t lds_bytes, bool waits) {
-    auto key = std::make_tuple(unroll * (inl ? 1 : -1), block, lds_bytes);
+int stream_grid(sg_ctx_s* ctx, int64_t ntiles, bool inl, bool lean, int unroll, int block, size_t lds_bytes, bool waits) {
+    auto key = std::make_tuple((unroll + (lean ? 8 : 0)) * (inl ? 1 : -1), block, lds_bytes);
     auto it = ctx->occupancy.find(key);
     int nb;
     if (it != ctx->occupancy.end()) {
         nb = it->second;
     } else {
-        nb = sg_stream_occupancy(unroll, inl, block, lds_bytes);
+        nb = sg_stream_occupancy(unroll, inl, lean, block, lds_bytes);
         ctx->occupancy[key] = nb;
     }
     const int64_t cap = (int64_t)coresident_blocks(nb, lds_blocks_per_cu(lds_bytes), waits) * ctx->num_cu;
     return (int)std::max<int64_t>(1, std::min<int64_t>(ntiles, cap));
+}
+
+// Lean: no compaction, at most two inputs, value operations, predicates and reductions on
+// register 0 (a zip's second operand in register 1), and no exp, division, constant or move.
+// for_all checks of a class or range test are fused with their predicate and may read
+// register 1.  Anything else runs on the general interpreter.
+std::vector<SgOp> lean_program(const InstPlan& ip) {
+    std::vector<SgOp> out;
+    if (ip.scan_space != 0 || (int)ip.sources.size() > LEAN_REGS || ip.nsum > LEAN_SUMS) return {};
+    for (size_t i = 0; i < ip.prog.size(); ++i) {
+        const SgOp& p = ip.prog[i];
+        if ((p.code == P_FINITE || p.code == P_RANGE_F || p.code == P_RANGE_I) && p.a < LEAN_REGS &&
+            i + 1 < ip.prog.size() && ip.prog[i + 1].code == CHK_ALL) {
+            const SgOp& c = ip.prog[i + 1];
+            SgOp f{};
+            f.code = CHK_PRED;
+            f.pad = p.code;
+            f.a = p.a;
+            f.c0 = p.c0;
+            f.c1 = p.c1;
+            f.sp = c.sp;
+            f.aux = c.aux;
+            out.push_back(f);
+            ++i;
+            continue;
+        }
+        switch (p.code) {
+            case F_ADD: case F_SUB: case F_MUL: case I_ADD: case I_SUB: case I_MUL:
+                if (p.a != 0 || p.b != 1) return {};
+                break;
+            case F_AFFINE: case F_ADDC: case F_MULC: case F_SQUARE: case F_NEG: case F_ABS: case F_SQRT: case F_SQRT_ABS:
+            case I_AFFINE: case I_ADDC: case I_MULC: case I_SQUARE: case I_NEG: case I_ABS: case I_TO_F:
+            case P_CMP_F: case P_CMP_I: case P_FINITE: case P_RANGE_F: case P_RANGE_I:
+            case CHK_SORTED_F: case CHK_SORTED_I:
+            case RED_SUM_F: case RED_ABSSUM_F: case RED_SUM_I: case RED_MAX_F: case RED_MIN_F: case RED_MAX_I: case RED_MIN_I:
+                if (p.a != 0) return {};
+                break;
+            case EMIT:
+                if (p.a != 0 || p.sp != 0) return {};
+                break;
+            case P_TRUE: case P_AND: case P_OR: case P_NOT: case FILTER: case CHK_ALL: case CHK_ANY: case RED_COUNT:
+                break;
+            default: return {};
+        }
+        out.push_back(p);
+    }
+    return out;
+}
+
+void set_lean(InstDesc& d, const std::vector<SgOp>& lean) {
+    d.prog_len = (int32_t)lean.size();
+    for (const SgOp& o : lean)
+        if (o.code == CHK_SORTED_F || o.code == CHK_SORTED_I) d.flags |= 2;
 }
 
 int inst_cemit(const InstPlan& ip) {
@@ -292,6 +345,7 @@ sg_status launch_program(sg_program_s* P, ExecSlot& es) {
     if (!P->plan.valid || P->plan.generation != ctx->generation) {
         sg_status st = build_plan(P, &P->plan);
         if (st != SG_OK) { P->plan.valid = false; return st; }
+        for (auto& ip : P->plan.insts) ip.lean = lean_program(ip);
     }
     Plan& plan = P->plan;
     const int block = P->block ? P->block : ctx->block;
@@ -300,7 +354,7 @@ sg_status launch_program(sg_program_s* P, ExecSlot& es) {
     // launch shape of one pass: unroll U, tiles of C sub-tiles, a grid of G resident blocks;
     // a pass whose per-lane accumulators and staging buffers would not fit in LDS runs with
     // a smaller unroll
-    struct Geo { int U, C, grid; int64_t ntiles; size_t lds; };
+    struct Geo { int U, C, grid; int64_t ntiles; size_t lds; bool lean; };
     std::vector<Geo> geo(plan.insts.size());
     std::vector<void*> jks(plan.insts.size(), nullptr);  // specialized kernels (compiled once, cached)
     int64_t max_tiles = 1;
@@ -308,7 +362,9 @@ sg_status launch_program(sg_program_s* P, ExecSlot& es) {
         const InstPlan& ip = plan.insts[i];
         Geo& g = geo[i];
         // a specialized kernel keeps its accumulators in registers: no LDS rows for them
-        const int ns = ctx->specialize ? 0 : (int)ip.slot_kind.size(), nu = ctx->specialize ? 0 : ip.nsum;
+        g.lean = !ctx->specialize && !ip.lean.empty() && block <= LEAN_BLOCK;
+        // (a lean one its sums)
+        const int ns = ctx->specialize ? 0 : (int)ip.slot_kind.size(), nu = ctx->specialize || g.lean ? 0 : ip.nsum;
         const int ce = inst_cemit(ip);
         for (g.U = unroll;; g.U /= 2) {
             // without a plan, a short vector's tiles are cut until they reach every CU twice
@@ -339,7 +395,7 @@ sg_status launch_program(sg_program_s* P, ExecSlot& es) {
             const int occ = coresident_blocks(jit_occupancy(jks[i], block, g.lds), lds_blocks_per_cu(g.lds), waits);
             g.grid = (int)std::max<int64_t>(1, std::min<int64_t>(g.ntiles, (int64_t)occ * ctx->num_cu));
         } else {
-            g.grid = stream_grid(ctx, g.ntiles, true, g.U, block, g.lds, waits);
+            g.grid = stream_grid(ctx, g.ntiles, true, g.lean, g.U, block, g.lds, waits);
         }
         max_tiles = std::max(max_tiles, g.ntiles);
     }
@@ -396,15 +452,17 @@ sg_status launch_program(sg_program_s* P, ExecSlot& es) {
             a.substeps = g.C;
             a.spread = MAX_SPREAD;
             a.lds_slots = jk ? 0 : (int)ip.slot_kind.size();
-            a.lds_sums = jk ? 0 : ip.nsum;
+            a.lds_sums = jk || g.lean ? 0 : ip.nsum;
             a.lds_cemit = inst_cemit(ip);
             a.epoch_val = next_epoch(ctx);
             a.wait_limit = ctx->wait_limit;
             fill_inst(ip, a.inst0, 0, g.ntiles, 0);
-            std::memcpy(a.prog0, ip.prog.data(), ip.prog.size() * sizeof(SgOp));
+            const std::vector<SgOp>& prog = g.lean ? ip.lean : ip.prog;
+            if (g.lean) set_lean(a.inst0, prog);
+            std::memcpy(a.prog0, prog.data(), prog.size() * sizeof(SgOp));
             const auto ev = t_launch(jk ? "stream_spec" : "stream");
             if (jk) SG_HIP(ctx, jit_launch(jk, a, g.grid, block, g.lds, ctx->stream, ev.first, ev.second));
-            else SG_HIP(ctx, sg_launch_stream(a, g.U, true, g.grid, block, g.lds, ctx->stream, ev.first, ev.second));
+            else SG_HIP(ctx, sg_launch_stream(a, g.U, true, g.lean, g.grid, block, g.lds, ctx->stream, ev.first, ev.second));
             ctx->last_grid = g.grid;
             ctx->last_block = block;
             ctx->last_unroll = g.U;

@@ -28,6 +28,9 @@ typedef unsigned long uintptr_t;
 namespace sg {
 
 constexpr int NREG = 5;            // value registers per element
+constexpr int LEAN_REGS = 2;       // value registers and inputs of a lean program
+constexpr int LEAN_SUMS = 2;       // and its float64 sums
+constexpr int LEAN_BLOCK = 256;    // largest block of the lean kernel
 constexpr int MAX_IN = 4;          // loaded sources per instance
 constexpr int MAX_OUT = 4;         // materialized outputs per instance
 constexpr int MAX_SLOTS = 16;      // exact accumulators per instance
@@ -70,7 +73,7 @@ enum OpCode : uint8_t {
     RED_COUNT,     // number of elements of space sp -> slot aux
     EMIT,          // write register a to output aux (space 0: dense; scan space: compacted)
     // a predicate and the CHK_ALL / CHK_ANY that pops it, as one operation (formed by the
-    // run-time compiler for checks outside the compacted space): predicate opcode in pad,
+    // run-time compiler and, for P_FINITE / P_RANGE_* with CHK_ALL, for lean programs; for checks outside the compacted space): predicate opcode in pad,
     // its comparison in sp2, register a, constants c0 / c1; dst 0 = for_all, 1 = exists;
     // space sp, slot aux.  Same result as the pair.
     CHK_PRED,
@@ -106,7 +109,7 @@ struct InstDesc {
     int32_t nsum;
     int32_t nslots;
     int32_t count_slot;     // slot holding the scan-space count (-1 if none)
-    int32_t flags;          // bit 0: every input/output 16-byte aligned
+    int32_t flags;          // bit 0: every input/output 16-byte aligned; bit 1: lean, checks sortedness
     uint8_t slot_kind[MAX_SLOTS];
 };
 

@@ -83,7 +83,7 @@ struct sg_ctx_s {
     sg::InstResult* host_results = nullptr;
     std::map<std::string, sgrt::KTime> times;
     std::vector<hipEvent_t> events;
-    std::map<std::tuple<int, int, size_t>, int> occupancy;  // (±unroll, block, LDS bytes) -> blocks per CU
+    std::map<std::tuple<int, int, size_t>, int> occupancy;  // (±unroll [+ 8: lean], block, LDS bytes) -> blocks per CU
 };
 
 struct sg_fn_s {
@@ -168,6 +168,7 @@ struct InstPlan {
     std::vector<AbsSum> abssums;
     std::vector<sg_node_s*> compacted;  // outputs whose count is the scan count
     int result_index = 0;               // slot in the results array
+    std::vector<sg::SgOp> lean;         // the program in the lean interpreter's form, or empty
     // specialized kernel of this pass (owned by the kernel cache) and the shape it was
     // compiled for; looked up again only when the shape changes
     void* jit = nullptr;
@@ -237,8 +238,13 @@ void fill_inst(const InstPlan& ip, sg::InstDesc& d, int64_t tile0, int64_t ntile
 void publish_inst(const InstPlan& ip, const sg::InstResult& r, bool publish_values);
 sg_status alloc_output(sg_ctx_s* ctx, sg_node_s* n);
 sg_status assemble_verdicts(sg_program_s* P, const sg::InstResult* results, std::vector<sg_verdict>& V);
-int stream_grid(sg_ctx_s* ctx, int64_t ntiles, bool inl, int unroll, int block, size_t lds_bytes, bool waits);
+int stream_grid(sg_ctx_s* ctx, int64_t ntiles, bool inl, bool lean, int unroll, int block, size_t lds_bytes, bool waits);
 int coresident_blocks(int occupancy, int lds_blocks, bool waits_on_others);
+// A pass's program in the lean interpreter's form (its checks fused), or empty when it needs the
+// general one.
+std::vector<sg::SgOp> lean_program(const InstPlan& ip);
+// a filled descriptor for the lean kernel and this program
+void set_lean(sg::InstDesc& d, const std::vector<sg::SgOp>& lean);
 // Launch shape of a pass: sub-tiles per tile (clamped when values are staged for
 // compaction) and the dynamic LDS bytes of its per-lane accumulators and staging regions.
 int inst_cemit(const InstPlan& ip);

@@ -23,7 +23,7 @@ using namespace sg;
 using namespace sgrt;
 
 extern "C" sg_status sg_mlp_predict(sg_mlp_s* m, const float* X_dev, int64_t n, float* Y_dev);
-int sg_stream_occupancy(int unroll, bool inl, int block, size_t lds_bytes);
+int sg_stream_occupancy(int unroll, bool inl, bool lean, int block, size_t lds_bytes);
 
 namespace {
 
@@ -158,7 +158,7 @@ sg_status features(sg_program_s* P, const sg_plan* plan, const std::vector<sg_no
         const int ns = spec ? 0 : (int)ip.slot_kind.size(), nu = spec ? 0 : ip.nsum, ce = inst_cemit(ip);
         const int C = stream_substeps(plan->substeps, plan->block, plan->unroll, ns, nu, ce, ip.scan_space != 0, 2);
         const size_t lds = stream_lds_bytes(ns, nu, ce, C, plan->block, plan->unroll, 2);
-        const int o = std::min(sg_stream_occupancy(plan->unroll, true, plan->block, lds), lds_blocks_per_cu(lds));
+        const int o = std::min(sg_stream_occupancy(plan->unroll, true, false, plan->block, lds), lds_blocks_per_cu(lds));
         occ = occ == 0 ? o : std::min(occ, o);
     }
     f[23] = (float)occ;  // resident blocks per CU of the tightest pass
