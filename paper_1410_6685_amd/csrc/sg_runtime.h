@@ -305,6 +305,7 @@ struct sg_mlp_s {
     sg_ctx_s* ctx = nullptr;
     float* P = nullptr;    // params | grad | Adam m | Adam v (device)
     double* loss = nullptr;
+    void* shared = nullptr;  // what the training workgroups exchange (device)
     int step = 0;
     bool norm_set = false;
     float mean[24], scale[24], lo[24], hi[24];

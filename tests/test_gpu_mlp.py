@@ -47,6 +47,26 @@ def test_training_tracks_oracle_and_converges(sg, ctx):
     assert more[-1] < 0.05 * gpu_losses[0]
 
 
+@pytest.mark.parametrize("n,batch", [(1, 1), (5, 7), (33, 16), (130, 17), (257, 128), (300, 127), (48, 3)])
+def test_training_batches_that_do_not_fill_the_workgroups(sg, ctx, n, batch):
+    """Batches smaller than, and no multiple of, the workgroups that share a step; partial last
+    batches; and a training resumed after an epoch equals one that ran through."""
+    X, T = W.mlp_synthetic_dataset(n, 70 + n)
+    p0 = W.mlp_init_params(14)
+    t = to_dev({"X": X, "T": T})
+    say("mlp train", n, batch)
+    net = sg.Mlp(ctx, p0)
+    losses = net.train(t["X"], t["T"], batch=batch, epochs=2, lr=1e-3)
+    p64, ref_losses = OM.adam_train(p0.astype(np.float64), X, T, batch=batch, epochs=2, lr=1e-3)
+    assert np.allclose(losses, ref_losses, rtol=1e-3)
+    p = net.params()
+    assert np.max(np.abs(p - p64)) <= 1e-4 * np.max(np.abs(p64))
+    twice = sg.Mlp(ctx, p0)
+    again = [twice.train(t["X"], t["T"], batch=batch, epochs=1, lr=1e-3)[0] for _ in range(2)]
+    assert np.array_equal(np.array(again), losses)
+    assert np.array_equal(twice.params().view(np.uint32), p.view(np.uint32))
+
+
 def test_predict_matches_oracle(sg, ctx):
     X, _ = W.mlp_synthetic_dataset(1000, 8)
     p0 = W.mlp_init_params(9)
