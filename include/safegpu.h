@@ -261,7 +261,8 @@ sg_status sg_quicksort(sg_node in, sg_node* out);
 /* Determinant of a square f32 matrix by Gaussian elimination (Section 5, Listing 5, in its
  * textbook form: partial pivoting, a zero pivot column means det = 0), in float64 on the
  * widened input, as a scalar node.  Built-in precondition rows = columns (SG_E_SHAPE).  The
- * elimination loop (3n + 1 kernels) is captured into a HIP graph once per node and replayed.
+ * elimination (panels of columns; above 4096 rows three kernels per column) is captured into a
+ * HIP graph once per node and replayed.
  * sg_scalar_get gives f = the determinant as a double (+-inf beyond its range), i = its sign;
  * sg_det_parts the exact representation. */
 sg_status sg_gauss_det(sg_node A, sg_node* out);

@@ -57,6 +57,50 @@ def test_det_special_matrices(sg, ctx):
     assert (s, m, e) == gauss_det(T)[:3]
 
 
+@pytest.mark.parametrize("n", [15, 16, 17, 31, 32, 48, 65, 511, 513, 528, 1023, 1025])
+def test_det_panel_edges_bit_exact(sg, ctx, n):
+    """Partial last panels, the panels' launch shapes (rows per thread, panel width), pivots that
+    tie in their high words, and columns whose only nonzero entry is subnormal."""
+    say("gauss panels", n)
+    A = W.normal_f32(n * n, 60 + n).reshape(n, n)
+    if n <= 65:
+        A = np.round(A * 2).astype(np.float32)  # ties in most columns
+        A[:, n // 2] = 0.0
+        A[n // 3, n // 2] = 1e-42
+        A += np.diag(np.full(n, 3.0, np.float32))
+    (s, m, e), _, _ = gpu_det(sg, ctx, A)
+    assert (s, m, e) == gauss_det(A)[:3]
+
+
+@pytest.mark.parametrize("n,col", [(16, 15), (40, 15), (40, 16), (40, 39), (600, 33), (1100, 1099)])
+def test_det_singular_in_any_panel(sg, ctx, n, col):
+    say("gauss singular", n, col)
+    A = np.triu(W.uniform_i32(n * n, 8, 1, 3).astype(np.float32).reshape(n, n))
+    A[col, col] = 0.0
+    A[col + 1:, col] = 0.0
+    (s, m, e), _, _ = gpu_det(sg, ctx, A)
+    assert (s, m, e) == (0, 0.0, 0)
+    A[3, 3] = np.nan  # a NaN pivot comes first and spreads
+    (s, m, e), _, _ = gpu_det(sg, ctx, A)
+    assert (s, np.isnan(m)) == (gauss_det(A)[0], np.isnan(gauss_det(A)[1]))
+
+
+@pytest.mark.parametrize("n", [1600, 2049, 2100])
+def test_det_of_a_permuted_triangular_matrix(sg, ctx, n):
+    """Sizes whose first panels hold four rows per thread, and are narrower above 2048 rows: every
+    pivot is the triangle's diagonal entry, found in another row, and no update changes it."""
+    say("gauss permuted", n)
+    U = np.triu(W.uniform_i32(n * n, 18, 1, 9).astype(np.float32).reshape(n, n))
+    perm = np.random.default_rng(n).permutation(n)
+    sign = round(np.linalg.slogdet(np.eye(n)[perm])[0])
+    mant, expo = 0.5, 1
+    for k in range(n):
+        mant, ex = np.frexp(mant * np.frexp(float(U[k, k]))[0])
+        expo += int(ex) + int(np.frexp(float(U[k, k]))[1])
+    (s, m, e), _, _ = gpu_det(sg, ctx, U[perm])
+    assert (s, m, e) == (sign, mant, expo)
+
+
 def test_graph_replay_follows_the_matrix(sg, ctx):
     import torch
     n = 200
