@@ -22,7 +22,9 @@ using namespace sg;
 
 hipError_t sg_launch_stream(const StreamArgs& a, int unroll, bool inl, bool lean, int grid, int block, size_t lds_bytes,
                             hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
-hipError_t sg_launch_gemm_f32(const float* A, const float* B, float* C, int64_t M, int64_t N, int64_t K, hipStream_t s);
+int sg_gemm_parts(int64_t M, int64_t N, int64_t K, int num_cu);
+hipError_t sg_launch_gemm_f32(const float* A, const float* B, float* C, int64_t M, int64_t N, int64_t K, int num_cu,
+                              float* work, hipStream_t s);
 hipError_t sg_launch_product_check(const float* C, const float* A, const float* B, const float* R, int64_t M,
                                    int64_t N, int64_t K, int64_t nvec, double tol, double* work, InstResult* res,
                                    hipStream_t s);
@@ -480,8 +482,15 @@ sg_status launch_program(sg_program_s* P, ExecSlot& es) {
             sg_node_s* C = step.C;
             if ((st = alloc_output(ctx, C)) != SG_OK) return st;
             t_begin("gemm");
-            SG_HIP(ctx, sg_launch_gemm_f32((const float*)step.A->dev, (const float*)step.B->dev, (float*)C->dev,
-                                           step.A->rows, step.B->cols, step.A->cols, ctx->stream));
+            const int64_t gm = step.A->rows, gn = step.B->cols, gk = step.A->cols;
+            const int parts = sg_gemm_parts(gm, gn, gk, ctx->num_cu);
+            float* work = nullptr;
+            if (parts > 1 && !(work = (float*)dev_alloc(ctx, (size_t)parts * gm * gn * 4)))
+                return fail(ctx, SG_E_OOM, "matrix product: work memory");
+            const hipError_t ge = sg_launch_gemm_f32((const float*)step.A->dev, (const float*)step.B->dev, (float*)C->dev, gm, gn,
+                                                     gk, ctx->num_cu, work, ctx->stream);
+            dev_free(ctx, work);  // reused in stream order only
+            SG_HIP(ctx, ge);
             t_end();
             C->count = C->n;
         } else {

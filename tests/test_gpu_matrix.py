@@ -35,6 +35,32 @@ def test_gemm_small_within_rounding_bound(sg, ctx, M, K, N):
     assert np.all(np.abs(C.astype(np.float64) - C64) <= bound)
 
 
+@pytest.mark.parametrize("M,K,N", [(1, 4096, 1), (64, 4096, 64), (65, 1000, 3), (63, 31, 64), (64, 32, 65), (3, 33, 129),
+                                   (127, 255, 1), (130, 257, 2), (1000, 1531, 777), (513, 640, 511), (2049, 33, 2049),
+                                   (2050, 17, 2047), (2048, 16, 2048), (4096, 1, 1024)])
+def test_gemm_tiles_parts_and_tails(sg, ctx, M, K, N):
+    """64- and 128-wide tiles, products cut along K, slices and rows that end anywhere, and a
+    row of NaN and a column of infinities that must not reach other entries."""
+    say("gemm tiles", M, K, N)
+    A = W.normal_f32(M * K, 31, 1.0 / np.sqrt(K)).reshape(M, K)
+    B = W.normal_f32(K * N, 32, 1.0 / np.sqrt(K)).reshape(K, N)
+    C64 = OM.matmul64(A, B)
+    bound = OM.gamma(K) * OM.matmul_bound(A, B)
+    assert np.all(np.abs(gemm(sg, ctx, A, B).astype(np.float64) - C64) <= bound)
+    A[-1] = np.nan
+    B[:, -1] = np.inf
+    C = gemm(sg, ctx, A, B)
+    assert np.all(np.isnan(C[-1])) and not np.any(np.isfinite(C[:, -1]))
+    assert np.all(np.abs(C[:-1, :-1].astype(np.float64) - C64[:-1, :-1]) <= bound[:-1, :-1])
+
+
+def test_gemm_empty_inner_dimension(sg, ctx):
+    import torch
+    c = ctx.wrap(torch.zeros((5, 0), device="cuda")).matmul(ctx.wrap(torch.zeros((0, 7), device="cuda")))
+    ctx.execute(c)
+    assert np.array_equal(c.to_host(), np.zeros(35, np.float32))
+
+
 def exact_up_to_zero_sign(got, want):
     """Bit-exact, except that a -0 entry may come out +0: the sum -0 + (+0) is +0 in IEEE
     arithmetic, in the float64 oracle as on the matrix cores."""
