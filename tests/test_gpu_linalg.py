@@ -116,3 +116,25 @@ def test_compwise_divide_with_builtin_clauses(sg, ctx, fused, case):
     with pytest.raises(sg.SafeGPUError) as e:
         ctx.wrap(to_dev({"i": np.ones(4, np.int32)})["i"]).zip(ctx.wrap(to_dev({"j": np.ones(4, np.int32)})["j"]), "div")
     assert e.value.status_name == "dtype"
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 1), (3, 1023), (3, 1024), (3, 1025), (4095, 5), (4096, 5), (4097, 1030), (31, 257),
+                                       (33, 2049), (100, 255), (65, 4099), (2, 5003), (300, 3)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_matvec_row_and_column_edges(sg, ctx, rows, cols, offset):
+    """Rows shared by one or four waves, stretches and chunks that end anywhere, unaligned rows:
+    the float64 sum of exact products, rounded once."""
+    import torch
+    say("matvec edges", rows, cols, offset)
+    M = W.normal_f32(rows * cols, 71).reshape(rows, cols)
+    v, u = W.normal_f32(cols, 72), W.normal_f32(rows, 73)
+    dev = torch.from_numpy(np.concatenate([np.zeros(offset, np.float32), M.ravel()])).cuda()[offset:].view(rows, cols)
+    m = ctx.wrap(dev)
+    tv, tu = to_dev({"v": v, "u": u}).values()
+    y, z = m.right_multiply(ctx.wrap(tv)), m.left_multiply(ctx.wrap(tu))
+    ctx.execute(y, z)
+    for got, a, b in ((y.to_host(), M, v), (z.to_host(), M.T, u)):
+        ex = a.astype(np.float64) @ b.astype(np.float64)
+        ab = np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64)
+        # half an ulp of the result, and the float64 additions of both sides
+        assert np.all(np.abs(got.astype(np.float64).ravel() - ex) <= 2.0 ** -24 * np.abs(ex) + 2.0 ** -40 * ab)
