@@ -19,9 +19,46 @@ namespace sgl {
 
 constexpr int TT = 64;  // transpose tile
 
+// Do the values fail a check?  Not finite: the bits reach 0x7F800000 as a signed integer (+inf,
+// positive NaNs) or 0xFF800000 as an unsigned one (-inf, negative NaNs).
+template <int K>
+__device__ __forceinline__ bool fails(const sgrt::FusedCheck& chk, const uint32_t (&x)[K]) {
+    bool bad = false;
+    for (int i = 0; i < chk.n; ++i) {
+        const sg::SgOp& op = chk.ops[i];
+        if (op.pad == sg::P_FINITE) {
+            int32_t ms = INT32_MIN;
+            uint32_t mu = 0u;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                ms = max(ms, (int32_t)x[k]);
+                mu = max(mu, x[k]);
+            }
+            bad |= ms >= 0x7F800000 || mu >= 0xFF800000u;
+        } else if (op.pad == sg::P_RANGE_F) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const float f = __builtin_bit_cast(float, x[k]);
+                bad |= !(f >= op.c0.f && f <= op.c1.f);
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < K; ++k) bad |= (int32_t)x[k] < op.c0.i || (int32_t)x[k] > op.c1.i;
+        }
+    }
+    return bad;
+}
+
+// CHECK: the contract's predicates are evaluated on the elements as they pass, so that the
+// contract's own pass reads the result again only when one fails (to find the first).
+template <bool CHECK>
 __global__ __launch_bounds__(256) void t_transpose(const uint32_t* __restrict__ a, uint32_t* __restrict__ b,
-                                                   int64_t rows, int64_t cols) {
+                                                   int64_t rows, int64_t cols, const sgrt::FusedCheck chk) {
     __shared__ uint32_t tile[TT][TT + 1];
+    auto report = [&](bool bad) {
+        if (__ballot(bad) && (threadIdx.x & 63) == 0)
+            __hip_atomic_store(chk.flag, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     const int64_t r0 = (int64_t)blockIdx.y * TT, c0 = (int64_t)blockIdx.x * TT;
     // a tile inside the matrix with 16-byte aligned rows: 16-byte reads of 16 rows and 16-byte
     // writes of 16 transposed rows per step (the same for the whole block)
@@ -36,6 +73,14 @@ __global__ __launch_bounds__(256) void t_transpose(const uint32_t* __restrict__ 
             uint32_t* t = &tile[tr + 16 * k][tc];
             t[0] = v[k].x; t[1] = v[k].y; t[2] = v[k].z; t[3] = v[k].w;
         }
+        if (CHECK) {
+            uint32_t x[TT / 4];
+#pragma unroll
+            for (int k = 0; k < TT / 16; ++k) {
+                x[4 * k + 0] = v[k].x; x[4 * k + 1] = v[k].y; x[4 * k + 2] = v[k].z; x[4 * k + 3] = v[k].w;
+            }
+            report(fails(chk, x));
+        }
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < TT / 16; ++k) {
@@ -47,11 +92,17 @@ __global__ __launch_bounds__(256) void t_transpose(const uint32_t* __restrict__ 
         return;
     }
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;  // 64 x 4 threads
+    bool bad = false;
 #pragma unroll
     for (int k = 0; k < TT / 4; ++k) {
         const int64_t r = r0 + ty + 4 * k, c = c0 + tx;
-        if (r < rows && c < cols) tile[ty + 4 * k][tx] = a[r * cols + c];
+        if (r < rows && c < cols) {
+            const uint32_t x[1] = {a[r * cols + c]};
+            tile[ty + 4 * k][tx] = x[0];
+            if (CHECK) bad |= fails(chk, x);
+        }
     }
+    if (CHECK) report(bad);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < TT / 4; ++k) {
@@ -187,7 +238,7 @@ __global__ __launch_bounds__(256) void mv_left_sum(const double* __restrict__ pa
 
 namespace sgrt {
 
-sg_status run_linalg(sg_ctx_s* ctx, sg_node_s* n) {
+sg_status run_linalg(sg_ctx_s* ctx, sg_node_s* n, const FusedCheck* check) {
     using namespace sgl;
     hipStream_t st = ctx->stream;
     if (n->op == OPN_TRANSPOSE) {
@@ -195,7 +246,12 @@ sg_status run_linalg(sg_ctx_s* ctx, sg_node_s* n) {
         const int64_t rows = a->rows, cols = a->cols;
         if (rows > 0 && cols > 0) {
             const dim3 grid((unsigned)((cols + TT - 1) / TT), (unsigned)((rows + TT - 1) / TT));
-            hipLaunchKernelGGL(t_transpose, grid, dim3(256), 0, st, (const uint32_t*)a->dev, (uint32_t*)n->dev, rows, cols);
+            if (check)
+                hipLaunchKernelGGL(t_transpose<true>, grid, dim3(256), 0, st, (const uint32_t*)a->dev, (uint32_t*)n->dev, rows,
+                                   cols, *check);
+            else
+                hipLaunchKernelGGL(t_transpose<false>, grid, dim3(256), 0, st, (const uint32_t*)a->dev, (uint32_t*)n->dev, rows,
+                                   cols, FusedCheck());
             SG_HIP(ctx, hipGetLastError());
         }
         n->count = n->n;

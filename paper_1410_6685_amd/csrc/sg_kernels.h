@@ -149,6 +149,8 @@ struct StreamArgs {
     int32_t lds_sums;           // per-lane float64 sums kept in LDS (max over instances)
     int32_t lds_cemit;          // compacted outputs staged in LDS (max over instances)
     uint32_t wait_limit;        // spin limit of bounded waits: 0 default, k > 0: k - 1 spins
+    uint64_t* skip;             // lean kernel, or null: a zero word means that no element fails any
+                                // check (the pass that wrote them looked), so none need be read
     const uint32_t* limit_ptr;  // batched launches: the same limit in a device word (or null)
     InstDesc inst0;             // single-instance launches: the instance
     SgOp prog0[MAX_INLINE_OPS]; // single-instance launches: its program

@@ -109,6 +109,7 @@ __global__ __launch_bounds__(LEAN_BLOCK, 4) void lean_kernel(const StreamArgs A)
                 plen = (int)SG_D32(prog_len);
                 const int64_t* n_dev = (const int64_t*)(uintptr_t)SG_D64(n_dev);
                 n = n_dev ? (int64_t)uload64(n_dev) : (int64_t)SG_D64(n);
+                if (INLINE && A.skip && uload64(A.skip) == 0) n = 0;
                 tile0 = (int64_t)SG_D64(tile0);
                 ntiles = (int64_t)SG_D64(ntiles);
                 nin = (int)SG_D32(nin);
@@ -419,6 +420,8 @@ __global__ __launch_bounds__(LEAN_BLOCK, 4) void lean_kernel(const StreamArgs A)
         ntl = INLINE ? 1 : ntl + 1;
     }
     if (cur >= 0) flush();
+    // the finalizing block has seen every block's words, so all of them have read the word
+    if (INLINE && A.skip && tid == 0 && (int64_t)blockIdx.x == (ntiles - 1) % (int64_t)gridDim.x) st_relaxed(A.skip, 0);
 }
 
 }  // namespace sg

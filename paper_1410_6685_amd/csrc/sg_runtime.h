@@ -327,8 +327,15 @@ sg_status run_node_step(sg_ctx_s* ctx, const Plan& plan, sg_node_s* n, sg::InstR
 sg_status run_quicksort(sg_ctx_s* ctx, const void* in, void* out, int64_t m, bool is_f32, int64_t* count);
 // determinant by Gaussian elimination (graph-captured loop); sets the node's scalar fields
 sg_status run_gauss(sg_ctx_s* ctx, sg_node_s* node);
-// transposition and matrix-vector products (linalg.hip)
-sg_status run_linalg(sg_ctx_s* ctx, sg_node_s* node);
+// Checks that a transposition evaluates on the elements it moves: *flag is set when one fails.
+struct FusedCheck {
+    static constexpr int kMax = 4;
+    int n = 0;
+    sg::SgOp ops[kMax];  // CHK_PRED operations on every element
+    uint64_t* flag = nullptr;
+};
+// transposition (optionally with checks) and matrix-vector products (linalg.hip)
+sg_status run_linalg(sg_ctx_s* ctx, sg_node_s* node, const FusedCheck* check = nullptr);
 void gauss_cache_free(sg_ctx_s* ctx, void* cache);
 const char* node_step_name(const sg_node_s* n);
 sg_status execute_program(sg_program_s* P, sg_verdict* v, int32_t cap, int32_t* nv);

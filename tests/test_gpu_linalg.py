@@ -138,3 +138,43 @@ def test_matvec_row_and_column_edges(sg, ctx, rows, cols, offset):
         ab = np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64)
         # half an ulp of the result, and the float64 additions of both sides
         assert np.all(np.abs(got.astype(np.float64).ravel() - ex) <= 2.0 ** -24 * np.abs(ex) + 2.0 ** -40 * ab)
+
+
+@pytest.mark.parametrize("rows,cols", [(64, 64), (128, 192), (130, 67), (257, 1028), (3, 5)])
+def test_checks_of_a_transposed_matrix(sg, ctx, rows, cols):
+    """Class and range tests of a transpose, evaluated while it is made: the first failing index
+    in the transpose's order, on the same program as elements start and stop failing."""
+    import torch
+    say("transpose checks", rows, cols)
+    M = W.normal_f32(rows * cols, 81).reshape(rows, cols)
+    t = torch.from_numpy(M.copy()).cuda()
+    T = ctx.wrap(t).transpose()
+    p = sg.Program(ctx)
+    p.add_root(T)
+    p.ensure_for_all(T, sg.Pred.isfinite())
+    p.ensure_for_all(T, sg.Pred.in_range(-50.0, 50.0))
+    for bad in ([], [(0, 0, np.nan)], [], [(rows - 1, cols - 1, -np.inf)], [(rows // 2, cols // 3, 51.0)], [],
+                [(rows - 1, 0, -51.0), (1, cols // 2, np.inf)]):
+        A = M.copy()
+        for r, c, x in bad:
+            A[r, c] = x
+        t.copy_(torch.from_numpy(A))
+        status, v = p.execute()
+        flat = A.T.ravel()
+        for got, ok in zip(v, (np.isfinite(flat), (flat >= -50) & (flat <= 50))):
+            first = int(np.argmin(ok)) if not ok.all() else -1
+            assert (got.holds, got.first_index) == (int(ok.all()), first)
+        assert status == ("ok" if not bad else "post_violated")
+        assert np.array_equal(T.to_host().view(np.uint32), flat.view(np.uint32))
+
+
+def test_checks_of_a_transposed_int_matrix(sg, ctx):
+    import torch
+    A = W.uniform_i32(100 * 68, 82, -9, 9).reshape(100, 68)
+    A[77, 3] = 10
+    T = ctx.wrap(torch.from_numpy(A).cuda()).transpose()
+    p = sg.Program(ctx)
+    p.add_root(T)
+    p.ensure_for_all(T, sg.Pred.in_range(-9, 9))
+    status, v = p.execute()
+    assert status == "post_violated" and v[0].first_index == 3 * 100 + 77
