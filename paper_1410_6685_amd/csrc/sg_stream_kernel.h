@@ -393,6 +393,7 @@ __device__ __forceinline__ void flush_instance(const StreamArgs& A, LDS& L, kptr
         double s = 0.0;
         for (int w = 0; w < nwaves; ++w) s += L.fin[w][tid];
         res->sum[tid] = s;
+        if (INLINE && A.host) A.host->sum[tid] = s;
     }
     const int count_slot = (int)d32<INLINE>(kdesc, D, (int)__builtin_offsetof(InstDesc, count_slot));
     for (int k = wave; k < ns; k += nwaves) {  // exact sums and maxima: any order
@@ -408,8 +409,15 @@ __device__ __forceinline__ void flush_instance(const StreamArgs& A, LDS& L, kptr
         if (lane == 0) {
             res->slot[k] = (int64_t)v;
             if (k == count_slot) res->scan_count = (int64_t)v;
+            if (INLINE && A.host) {
+                A.host->slot[k] = (int64_t)v;
+                if (k == count_slot) A.host->scan_count = (int64_t)v;
+            }
         }
     }
+    // every block's error bits were set before its words were published
+    if (INLINE && A.host && tid == 0)
+        A.host->err = __hip_atomic_load(&res->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
 }
 
