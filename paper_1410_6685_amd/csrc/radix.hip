@@ -15,9 +15,9 @@
 // another block: a single-pass scheme saves r_hist's read (4 of 12 bytes per item and pass) but
 // its blocks poll each other's prefixes across the XCDs' L2s.
 //
-// 10^8 float32 (four passes), with both postconditions: 2.21 ms; 13.9 ms by the recursion's
-// levels.  Per pass r_hist 80 us (5.0 TB/s), r_scan 6 us, r_scatter 411 us (1.9 TB/s, bound by
-// the ranks).  200,003 int32 in [-25000, 25000] (two passes): 113 us, before 763 us.
+// 10^8 float32 (four passes), with both postconditions: 1.76 ms; 13.9 ms by the recursion's
+// levels.  Per pass r_hist 80 us (5.0 TB/s), r_scan 6 us, r_scatter 320 us (2.5 TB/s, bound by
+// the ranks).  200,003 int32 in [-25000, 25000] (two passes): 72 us, before 763 us.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -165,9 +165,12 @@ __global__ __launch_bounds__(256) void r_scan(uint32_t* __restrict__ cnt, uint32
 // consecutive items of the tile; a row's items of equal digit find each other by eight ballots
 // (one per digit bit), so an item's rank is its wave's count of the digit so far plus the lanes
 // below it: no lane-order assumption on LDS atomics, and stable.  The tile is then staged in
-// LDS in digit order, so that a digit's items leave as one contiguous run.
+// LDS in digit order, so that a digit's items leave as one contiguous run.  Registers are held
+// to 128 for two workgroups per CU: each hides the other's barriers and rank chains (10^8
+// float32: 411 us a pass with 133 registers and one workgroup, 320 with two; three, at 80
+// registers with spills, 420).
 template <bool F, int I>
-__global__ __launch_bounds__(RB) void r_scatter(const uint32_t* __restrict__ a, uint32_t* __restrict__ out, int64_t n,
+__global__ __launch_bounds__(RB, I == 4 ? 2 : 4) void r_scatter(const uint32_t* __restrict__ a, uint32_t* __restrict__ out, int64_t n,
                                                 int64_t chunk, uint32_t bias, int shift,
                                                 const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ tot) {
     constexpr int TILE = RB * I;
