@@ -24,6 +24,7 @@
 namespace sg {
 
 struct LeanLds {
+    static constexpr int kSums = LEAN_SUMS;
     uint64_t slot[LEAN_BLOCK / 64][MAX_SLOTS];
     double sum[LEAN_BLOCK / 64][LEAN_SUMS];
     double tsum[TILE_BUF][LEAN_SUMS];

@@ -254,6 +254,11 @@ __device__ __forceinline__ uint8_t d8_lane(kptr kb, const char* gb, int off) {  
 }
 
 struct Lds {
+#ifdef __HIPCC_RTC__
+    static constexpr int kSums = SG_GEN_NSUMS > 0 ? SG_GEN_NSUMS : 1;  // of the one program
+#else
+    static constexpr int kSums = MAX_SUMS;
+#endif
     double exptab[1 << SG_EXPF_BITS];        // 2^(j/256) for the exp fast path
     uint64_t slot[MAX_WAVES][MAX_SLOTS];     // per-wave combines of the per-lane accumulators
     double sum[MAX_WAVES][MAX_SUMS];         // per-wave sums of the current tile
@@ -294,7 +299,8 @@ __device__ __forceinline__ void flush_instance(const StreamArgs& A, LDS& L, kptr
     for (int k = 0; k < ns; ++k) {
         const uint8_t kind = d8_lane<INLINE>(kdesc, D, (int)__builtin_offsetof(InstDesc, slot_kind) + k);
         uint64_t v = acc_take(k);
-        v = kind == SLOT_ADD ? (uint64_t)wave_sum_i64((int64_t)v) : wave_max_u64(v);
+        // a check that held left zero in every lane
+        if (__ballot(v != 0)) v = kind == SLOT_ADD ? (uint64_t)wave_sum_i64((int64_t)v) : wave_max_u64(v);
         if (lane == 0) L.slot[wave][k] = v;
     }
     __syncthreads();
@@ -343,7 +349,7 @@ __device__ __forceinline__ void flush_instance(const StreamArgs& A, LDS& L, kptr
     if (!has_last) return;
     // ---- finalize the instance ----
     // Everything read here was written by other blocks, past this XCD's L2: a round trip per
-    // dependent load.  Four words per thread are in flight at a time, and a slot's copies lie
+    // dependent load.  So each word is read once and many at a time, and a slot's copies lie
     // across the lanes of a wave (read one after another by one thread they took 8 us of a 37 us
     // execution over 1000 elements, and 20 of the 265 us of the 2^26 filter pass).
     InstResult* res = A.results + cur;
@@ -351,42 +357,53 @@ __device__ __forceinline__ void flush_instance(const StreamArgs& A, LDS& L, kptr
     // one per tile of the instance
     const int64_t nq = INLINE ? (int64_t)gridDim.x : ntiles;
     const int64_t q0 = INLINE ? 0 : tile0;
-    for (uint32_t spins = 0;; ++spins) {
-        if (spins >= wlimit) {  // bounded: report instead of hanging
-            if (tid == 0) atomicOr(&res->err, (uint32_t)ERR_FINALIZE_TIMEOUT);
-            break;
-        }
-        int ok = 1;
-        for (int w = 0; w < words; ++w)
-            for (int64_t q = tid; q < nq; q += 4 * B) {
-                uint64_t x[4];
+    // Thread t takes word sets t, t + B, ...: it loads a set's words together, again until all
+    // carry this launch's epoch, and adds the set's sums at once (in the order of the blocks or
+    // tiles), four sets in flight.
+    {
+        double s[LDS::kSums];
+#pragma unroll
+        for (int k = 0; k < LDS::kSums; ++k) s[k] = 0.0;
+        uint32_t spins = 0;
+        bool late = false;
+        for (int64_t q = tid; q < nq && !late; q += 4 * B) {
+            uint64_t x[4][1 + 2 * LDS::kSums];
+            for (;;) {
+                bool ok = true;
+                if (spins >= wlimit) {  // bounded: report instead of hanging
+                    late = true;
+                    break;
+                }
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    x[j] = q + j * B < nq ? ld_relaxed(&A.tags[(q0 + q + j * B) * TAG_WORDS + w]) : tag_word(epoch, 0);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) ok &= (uint32_t)(x[j] >> 32) == epoch;
-            }
-        if (__syncthreads_and(ok)) break;
-        __builtin_amdgcn_s_sleep(2);
-    }
-    for (int k = 0; k < nsum; ++k) {
-        double s = 0.0;
-        for (int64_t q = tid; q < nq; q += 4 * B) {
-            uint64_t lo[4], hi[4];
+                    for (int w = 0; w < 1 + 2 * LDS::kSums; ++w)
+                        if (w < words)
+                            x[j][w] = q + j * B < nq ? ld_relaxed(&A.tags[(q0 + q + j * B) * TAG_WORDS + w]) : tag_word(epoch, 0);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint64_t* tw = A.tags + (q0 + q + j * B) * TAG_WORDS + 1 + 2 * k;
-                lo[j] = q + j * B < nq ? ld_relaxed(tw) : 0;
-                hi[j] = q + j * B < nq ? ld_relaxed(tw + 1) : 0;
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int w = 0; w < 1 + 2 * LDS::kSums; ++w)
+                        if (w < words) ok &= (uint32_t)(x[j][w] >> 32) == epoch;
+                if (ok) break;
+                ++spins;
+                __builtin_amdgcn_s_sleep(2);
             }
-            // in the order of the blocks (or tiles)
+            if (late) break;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (q + j * B < nq)
-                    s += __builtin_bit_cast(double, ((hi[j] & 0xFFFFFFFFull) << 32) | (lo[j] & 0xFFFFFFFFull));
+#pragma unroll
+                for (int k = 0; k < LDS::kSums; ++k)
+                    if (k < nsum && q + j * B < nq)
+                        s[k] += __builtin_bit_cast(double, ((x[j][2 + 2 * k] & 0xFFFFFFFFull) << 32) | (x[j][1 + 2 * k] & 0xFFFFFFFFull));
         }
-        s = wave_sum_f64(s);
-        if (lane == 0) L.fin[wave][k] = s;
+        if (late) atomicOr(&res->err, (uint32_t)ERR_FINALIZE_TIMEOUT);
+#pragma unroll
+        for (int k = 0; k < LDS::kSums; ++k)
+            if (k < nsum) {
+                const double t = wave_sum_f64(s[k]);
+                if (lane == 0) L.fin[wave][k] = t;
+            }
     }
     __syncthreads();
     if (tid < nsum) {
@@ -405,7 +422,7 @@ __device__ __forceinline__ void flush_instance(const StreamArgs& A, LDS& L, kptr
             v = kind == SLOT_ADD ? v + x : (x > v ? x : v);
             if (x) st_relaxed(g + j, 0);
         }
-        v = kind == SLOT_ADD ? (uint64_t)wave_sum_i64((int64_t)v) : wave_max_u64(v);
+        if (__ballot(v != 0)) v = kind == SLOT_ADD ? (uint64_t)wave_sum_i64((int64_t)v) : wave_max_u64(v);
         if (lane == 0) {
             res->slot[k] = (int64_t)v;
             if (k == count_slot) res->scan_count = (int64_t)v;
