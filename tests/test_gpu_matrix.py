@@ -54,6 +54,43 @@ def test_gemm_tiles_parts_and_tails(sg, ctx, M, K, N):
     assert np.all(np.abs(C[:-1, :-1].astype(np.float64) - C64[:-1, :-1]) <= bound[:-1, :-1])
 
 
+@pytest.mark.parametrize("M,K,N", [(2048, 512, 1700), (1921, 513, 1793), (2050, 1000, 2047), (3713, 520, 3800)])
+def test_gemm_parts_of_values(sg, ctx, M, K, N):
+    """The product on bfloat16 parts (tiles of 128 and 256, slices and rows that end anywhere):
+    the float32 bound, exact products of values by powers of two, and magnitudes at the limits
+    of the parts' range."""
+    say("gemm parts", M, K, N)
+    A = W.normal_f32(M * K, 31, 1.0 / np.sqrt(K)).reshape(M, K)
+    B = W.normal_f32(K * N, 32, 1.0 / np.sqrt(K)).reshape(K, N)
+    A[:, ::3] *= np.float32(2.0 ** 40)
+    B[::3] *= np.float32(2.0 ** -25)
+    B[1::3] *= np.float32(2.0 ** 50)
+    A[np.abs(A) < 2.0 ** -40] = 0
+    B[np.abs(B) < 2.0 ** -40] = 0
+    C64, bound = OM.matmul64(A, B), OM.gamma(K) * OM.matmul_bound(A, B)
+    assert np.all(np.abs(gemm(sg, ctx, A, B).astype(np.float64) - C64) <= bound)
+    S = np.zeros((K, N), np.float32)
+    S[np.arange(N) % K, np.arange(N)] = np.float32(2.0) ** (np.arange(N) % 61 - 30)
+    assert np.array_equal(gemm(sg, ctx, A, S), A[:, np.arange(N) % K] * S[np.arange(N) % K, np.arange(N)])
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf, 3e38, 2.0 ** 60, 2.0 ** -41, 1e-42])
+@pytest.mark.parametrize("side", ["A", "B"])
+def test_gemm_value_without_parts(sg, ctx, value, side):
+    """One entry outside the parts' range: the product is that of the FP32 kernel."""
+    M, K, N = 1920, 512, 1920
+    say("gemm without parts", value, side)
+    A = W.normal_f32(M * K, 31, 1.0 / np.sqrt(K)).reshape(M, K)
+    B = W.normal_f32(K * N, 32, 1.0 / np.sqrt(K)).reshape(K, N)
+    (A if side == "A" else B)[300, 77] = value
+    C = gemm(sg, ctx, A, B).astype(np.float64)
+    with np.errstate(invalid="ignore", over="ignore"):
+        C64, bound = OM.matmul64(A, B), OM.gamma(K) * OM.matmul_bound(A, B)
+    ok = np.isfinite(C64) & (np.abs(C64) < 3e38)
+    assert np.array_equal(np.isnan(C[~ok]), np.isnan(C64[~ok]))
+    assert np.all(np.abs(C[ok] - C64[ok]) <= bound[ok])
+
+
 def test_gemm_empty_inner_dimension(sg, ctx):
     import torch
     c = ctx.wrap(torch.zeros((5, 0), device="cuda")).matmul(ctx.wrap(torch.zeros((0, 7), device="cuda")))
