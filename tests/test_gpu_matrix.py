@@ -204,3 +204,28 @@ def test_gemm_then_stream_pass(sg, ctx):
     status, _ = prog.execute()
     Cg = c.to_host()
     assert s.scalar()[1] == int(np.count_nonzero(Cg > 0))
+
+
+@pytest.mark.parametrize("M,K,N", [(1, 1, 1), (15, 513, 17), (17, 511, 1023), (1000, 1531, 777),  # made where staged
+                                   (1023, 1025, 1024), (2047, 1024, 1025), (3, 1 << 18, 16), (1 << 18, 3, 16)])
+def test_product_check_shapes(sg, ctx, M, K, N):
+    """Row and column remainders of the check's passes, on both sides of the size from which the
+    right-hand sides are written first.  Entries are whole numbers, so every sum is exact: the true
+    product has measure 0, and with positive probes a wrong row is reported at its index."""
+    g = np.random.default_rng(M + K + N)
+    A = g.integers(-2, 3, size=(M, K)).astype(np.float32)
+    B = g.integers(-2, 3, size=(K, N)).astype(np.float32)
+    R = g.integers(1, 4, size=(3, N)).astype(np.float32)
+    C = (A.astype(np.float64) @ B.astype(np.float64)).astype(np.float32)
+    for row in (None, 0, M // 2, M - 1):
+        Cc = C.copy()
+        if row is not None:
+            Cc[row, N - 1] += 1e6
+            Cc[M - 1, 0] = np.nan
+        say("product check", M, K, N, row)
+        built = sg.build_spec(ctx, _product_spec(M, K, N, 3), to_dev({"A": A, "B": B, "C": Cc, "R": R}))
+        v = built.program.execute()[1][0]
+        if row is None:
+            assert v.holds and v.measure == 0.0
+        else:
+            assert not v.holds and v.first_index == row
