@@ -15,12 +15,13 @@
 // another block: a single-pass scheme saves r_hist's read (4 of 12 bytes per item and pass) but
 // its blocks poll each other's prefixes across the XCDs' L2s.
 //
-// 10^8 float32 (four passes), with both postconditions: 1.76 ms; 13.9 ms by the recursion's
-// levels.  Per pass r_hist 80 us (5.0 TB/s), r_scan 6 us, r_scatter 320 us (2.5 TB/s, bound by
-// the ranks).  200,003 int32 in [-25000, 25000] (two passes): 72 us, before 763 us.
+// 10^8 float32 (four passes), with both postconditions: 1.57 ms; 13.9 ms by the recursion's
+// levels.  Per pass r_hist 95-105 us (4 TB/s), r_scan 6 us, r_scatter 246 us (3.3 TB/s; 163 us
+// would be a copy's).  200,003 int32 in [-25000, 25000] (two passes): 71 us, before 763 us.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "sg_runtime.h"
 
@@ -168,11 +169,16 @@ __global__ __launch_bounds__(256) void r_scan(uint32_t* __restrict__ cnt, uint32
 // LDS in digit order, so that a digit's items leave as one contiguous run.  Registers are held
 // to 128 for two workgroups per CU: each hides the other's barriers and rank chains (10^8
 // float32: 411 us a pass with 133 registers and one workgroup, 320 with two; three, at 80
-// registers with spills, 420).
+// registers with spills, 420).  Vector instructions fill two thirds of it, so the ballots' part
+// is kept to four a bit (bit, comparison, two three-input logic operations), whole tiles have no
+// conditions, and LDS reads go in batches: 296 -> 246 us.  Finding equal digits by atomic ORs of
+// lane masks in LDS is no faster on spread digits and half as fast on equal ones; loading the
+// next tile ahead spills.
 template <bool F, int I>
-__global__ __launch_bounds__(RB, I == 4 ? 2 : 4) void r_scatter(const uint32_t* __restrict__ a, uint32_t* __restrict__ out, int64_t n,
-                                                int64_t chunk, uint32_t bias, int shift,
-                                                const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ tot) {
+__global__ __launch_bounds__(RB, I == 4 ? 2 : 4) void r_scatter(const uint32_t* __restrict__ a, uint32_t* __restrict__ out,
+                                                               int64_t n, int64_t chunk, uint32_t bias, int shift,
+                                                               const uint32_t* __restrict__ cnt,
+                                                               const uint32_t* __restrict__ tot) {
     constexpr int TILE = RB * I;
     __shared__ uint32_t stage[TILE];
     __shared__ uint32_t wh[RW][RD];   // per wave: counts, then first place in the staged tile
@@ -193,13 +199,15 @@ __global__ __launch_bounds__(RB, I == 4 ? 2 : 4) void r_scatter(const uint32_t* 
     uint32_t gnext = digit_excl(tid < RD ? tot[tid] : 0u);  // of digit tid, kept by its thread
     if (tid < RD) gnext += cnt[(int64_t)tid * gridDim.x + blockIdx.x];
     const int64_t lo = (int64_t)blockIdx.x * chunk, hi = std::min<int64_t>(lo + chunk, n);
-    for (int64_t t0 = lo; t0 < hi; t0 += TILE) {
-        const int m = (int)std::min<int64_t>(TILE, hi - t0);
+    const int first = wave * 64 * I + lane;
+    auto tile = [&](auto full, int64_t t0) {
+        constexpr bool FULL = decltype(full)::value;
+        const int m = FULL ? TILE : (int)(hi - t0);
         uint32_t x[I];
-        const int first = wave * 64 * I + lane;
-        if (m == TILE) {
+        // read once: left out of the L2's lines, which collect the runs being written
+        if (FULL) {
 #pragma unroll
-            for (int i = 0; i < I; ++i) x[i] = a[t0 + first + 64 * i];
+            for (int i = 0; i < I; ++i) x[i] = __builtin_nontemporal_load(a + t0 + first + 64 * i);
         } else {
 #pragma unroll
             for (int i = 0; i < I; ++i) x[i] = first + 64 * i < m ? a[t0 + first + 64 * i] : 0u;
@@ -211,23 +219,30 @@ __global__ __launch_bounds__(RB, I == 4 ? 2 : 4) void r_scatter(const uint32_t* 
 #pragma unroll
         for (int i = 0; i < I; ++i) {
             uint32_t d = ((rkey<F>(x[i]) - bias) >> shift) & (RD - 1);
-            if (m != TILE && first + 64 * i >= m) d = RD - 1;
+            if (!FULL && first + 64 * i >= m) d = RD - 1;
             uint32_t mlo = ~0u, mhi = ~0u;
+            int32_t sb[8];
+            uint64_t bal[8];
 #pragma unroll
             for (int b = 0; b < 8; ++b) {
-                const int32_t s = __builtin_amdgcn_sbfe((int)d, b, 1);
-                const uint64_t bal = __ballot(s != 0);
-                mlo &= ~((uint32_t)bal ^ (uint32_t)s);
-                mhi &= ~((uint32_t)(bal >> 32) ^ (uint32_t)s);
+                sb[b] = __builtin_amdgcn_sbfe((int)d, b, 1);
+                asm("" : "+v"(sb[b]));  // else the comparison gets a shift of its own
+                bal[b] = __ballot(sb[b] != 0);
+            }
+            // m & ~(ballot ^ s) in one operation
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                mlo = __builtin_amdgcn_bitop3_b32(mlo, (uint32_t)bal[b], (uint32_t)sb[b], 0x90);
+                mhi = __builtin_amdgcn_bitop3_b32(mhi, (uint32_t)(bal[b] >> 32), (uint32_t)sb[b], 0x90);
             }
             const uint32_t below = __builtin_amdgcn_mbcnt_hi(mhi, __builtin_amdgcn_mbcnt_lo(mlo, 0u));
             // the wave's LDS accesses keep their order: every lane of the row reads the count
-            // before the group's first lane advances it
+            // before the group's first lane advances it (an add: nothing waits for the read)
             const uint32_t prev = __hip_atomic_load(&wh[wave][d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             __builtin_amdgcn_wave_barrier();
             if (below == 0)
-                __hip_atomic_store(&wh[wave][d], prev + (uint32_t)(__builtin_popcount(mlo) + __builtin_popcount(mhi)),
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                __hip_atomic_fetch_add(&wh[wave][d], (uint32_t)(__builtin_popcount(mlo) + __builtin_popcount(mhi)),
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             __builtin_amdgcn_wave_barrier();
             rd[i] = (prev + below) | (d << 16);
         }
@@ -249,19 +264,32 @@ __global__ __launch_bounds__(RB, I == 4 ? 2 : 4) void r_scatter(const uint32_t* 
             gnext += mine;
         }
         __syncthreads();
+        uint32_t q[I];
 #pragma unroll
-        for (int i = 0; i < I; ++i) stage[wh[wave][rd[i] >> 16] + (rd[i] & 0xFFFFu)] = x[i];
+        for (int i = 0; i < I; ++i) q[i] = wh[wave][rd[i] >> 16];
+#pragma unroll
+        for (int i = 0; i < I; ++i) stage[q[i] + (rd[i] & 0xFFFFu)] = x[i];
         __syncthreads();
+        constexpr int G = I < 8 ? I : 8;  // LDS reads in flight
 #pragma unroll
-        for (int i = 0; i < I; ++i) {
-            const int p = tid + RB * i;
-            if (p < m) {
-                const uint32_t v = stage[p];
-                out[goff[((rkey<F>(v) - bias) >> shift) & (RD - 1)] + (uint32_t)p] = v;
+        for (int i0 = 0; i0 < I; i0 += G) {
+            uint32_t v[G], g[G];
+#pragma unroll
+            for (int i = 0; i < G; ++i) v[i] = stage[tid + RB * (i0 + i)];
+#pragma unroll
+            for (int i = 0; i < G; ++i) g[i] = goff[((rkey<F>(v[i]) - bias) >> shift) & (RD - 1)];
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+                const int p = tid + RB * (i0 + i);
+                if (FULL || p < m) out[g[i] + (uint32_t)p] = v[i];
             }
         }
         // the next tile's counters and staging overwrite what this one reads only after its
         // own first barriers: wh after the barrier above, goff and stage after two more
+    };
+    for (int64_t t0 = lo; t0 < hi; t0 += TILE) {
+        if (t0 + TILE <= hi) tile(std::true_type{}, t0);
+        else tile(std::false_type{}, t0);
     }
 }
 
