@@ -359,15 +359,40 @@ __device__ __forceinline__ void flush_instance(const StreamArgs& A, LDS& L, kptr
     const int64_t q0 = INLINE ? 0 : tile0;
     // Thread t takes word sets t, t + B, ...: it loads a set's words together, again until all
     // carry this launch's epoch, and adds the set's sums at once (in the order of the blocks or
-    // tiles), four sets in flight.
-    {
+    // tiles), F sets in flight.
+    constexpr int F = 4;
+    if constexpr (!INLINE && LDS::kSums == MAX_SUMS) {
+        // The interpreter over many instances holds its next inputs in registers here, so two words
+        // at a time: with sets in flight its launches of more than 256 threads spilled (600 chains
+        // of 2^8 to 2^18 elements, 512 threads, unroll 4: 407 us so, 224 as it is).
+        uint32_t spins = 0;
+        for (int k = 0; k < max(nsum, 1); ++k) {
+            const int w0 = nsum ? 1 + 2 * k : 0, w1 = nsum ? w0 + 1 : 0;
+            double s = 0.0;
+            for (int64_t q = tid; q < nq; q += B) {
+                const uint64_t* t = A.tags + (q0 + q) * TAG_WORDS;
+                uint64_t lo, hi;
+                for (;;) {
+                    lo = ld_relaxed(t + w0);
+                    hi = ld_relaxed(t + w1);
+                    if (((uint32_t)(lo >> 32) == epoch && (uint32_t)(hi >> 32) == epoch) || spins >= wlimit) break;
+                    ++spins;
+                    __builtin_amdgcn_s_sleep(2);
+                }
+                s += __builtin_bit_cast(double, ((hi & 0xFFFFFFFFull) << 32) | (lo & 0xFFFFFFFFull));
+            }
+            s = wave_sum_f64(s);
+            if (lane == 0 && k < nsum) L.fin[wave][k] = s;
+        }
+        if (spins >= wlimit) atomicOr(&res->err, (uint32_t)ERR_FINALIZE_TIMEOUT);  // bounded: report instead of hanging
+    } else {
         double s[LDS::kSums];
 #pragma unroll
         for (int k = 0; k < LDS::kSums; ++k) s[k] = 0.0;
         uint32_t spins = 0;
         bool late = false;
-        for (int64_t q = tid; q < nq && !late; q += 4 * B) {
-            uint64_t x[4][1 + 2 * LDS::kSums];
+        for (int64_t q = tid; q < nq && !late; q += F * B) {
+            uint64_t x[F][1 + 2 * LDS::kSums];
             for (;;) {
                 bool ok = true;
                 if (spins >= wlimit) {  // bounded: report instead of hanging
@@ -375,13 +400,13 @@ __device__ __forceinline__ void flush_instance(const StreamArgs& A, LDS& L, kptr
                     break;
                 }
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+                for (int j = 0; j < F; ++j)
 #pragma unroll
                     for (int w = 0; w < 1 + 2 * LDS::kSums; ++w)
                         if (w < words)
                             x[j][w] = q + j * B < nq ? ld_relaxed(&A.tags[(q0 + q + j * B) * TAG_WORDS + w]) : tag_word(epoch, 0);
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+                for (int j = 0; j < F; ++j)
 #pragma unroll
                     for (int w = 0; w < 1 + 2 * LDS::kSums; ++w)
                         if (w < words) ok &= (uint32_t)(x[j][w] >> 32) == epoch;
@@ -391,7 +416,7 @@ __device__ __forceinline__ void flush_instance(const StreamArgs& A, LDS& L, kptr
             }
             if (late) break;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < F; ++j)
 #pragma unroll
                 for (int k = 0; k < LDS::kSums; ++k)
                     if (k < nsum && q + j * B < nq)
