@@ -92,17 +92,18 @@ __global__ __launch_bounds__(256) void t_transpose(const uint32_t* __restrict__ 
         return;
     }
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;  // 64 x 4 threads
-    bool bad = false;
+    // places outside the matrix take the tile's first element, which is checked with the others:
+    // loads and check without a condition around each (10^6 x 1 with its check 91 -> 59 us)
+    const uint32_t first = a[r0 * cols + c0];
+    uint32_t x[TT / 4];
 #pragma unroll
     for (int k = 0; k < TT / 4; ++k) {
         const int64_t r = r0 + ty + 4 * k, c = c0 + tx;
-        if (r < rows && c < cols) {
-            const uint32_t x[1] = {a[r * cols + c]};
-            tile[ty + 4 * k][tx] = x[0];
-            if (CHECK) bad |= fails(chk, x);
-        }
+        x[k] = r < rows && c < cols ? a[r * cols + c] : first;
     }
-    if (CHECK) report(bad);
+#pragma unroll
+    for (int k = 0; k < TT / 4; ++k) tile[ty + 4 * k][tx] = x[k];
+    if (CHECK) report(fails(chk, x));
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < TT / 4; ++k) {
@@ -143,15 +144,32 @@ __global__ __launch_bounds__(256) void mv_right(const float* __restrict__ M, con
 #pragma unroll
         for (int q = 0; q < 4; ++q) acc[q] = fma4(a[q], b[q], acc[q]);
     }
-    // the stretch that the row's end cuts belongs to one wave
-    for (; k < cols; k += 64 * 4) {
-        if (WPR > 1 && k / 1024 % WPR != wave) break;
-        const int64_t c = k + lane * 4;
-        if (c + 4 <= cols) {
-            acc[0] = fma4(*reinterpret_cast<const f4*>(m + c), *reinterpret_cast<const f4*>(v + c), acc[0]);
-        } else {
-            for (int64_t j = c; j < cols; ++j) acc[0] = __builtin_fma((double)m[j], (double)v[j], acc[0]);
+    // the stretch that the row's end cuts belongs to one wave: its loads are issued together too
+    // (places past the end read the row's last four columns and count as zero)
+    if (k < cols && (WPR == 1 || k / 1024 % WPR == wave)) {
+        if (cols >= 4) {
+            f4 a[4], b[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (k + q * 256 >= cols) break;  // (the same for the whole wave)
+                const int64_t c = std::min<int64_t>(k + q * 256 + lane * 4, cols - 4);
+                a[q] = *reinterpret_cast<const f4*>(m + c);
+                b[q] = *reinterpret_cast<const f4*>(v + c);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (k + q * 256 >= cols) break;
+                const bool in = k + q * 256 + lane * 4 + 4 <= cols;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    a[q][e] = in ? a[q][e] : 0.f;
+                    b[q][e] = in ? b[q][e] : 0.f;
+                }
+                acc[q] = fma4(a[q], b[q], acc[q]);
+            }
         }
+        const int64_t j = cols / 4 * 4 + lane;
+        if (j < cols) acc[0] = __builtin_fma((double)m[j], (double)v[j], acc[0]);
     }
     double s = (acc[0] + acc[1]) + (acc[2] + acc[3]);
 #pragma unroll
@@ -165,11 +183,28 @@ __global__ __launch_bounds__(256) void mv_right(const float* __restrict__ M, con
     if (threadIdx.x == 0) y[row] = (float)((part[0] + part[1]) + (part[2] + part[3]));
 }
 
+// y = M v for rows of at most 512 columns: 16 lanes a row, four columns a lane and step.  A wave per row
+// leaves most lanes idle: 10^6 x 1 162 -> 41 us, 100000 x 65 35 -> 18, 20000 x 500 21 -> 19 (1000 columns 24 -> 27).
+__global__ __launch_bounds__(256) void mv_right_narrow(const float* __restrict__ M, const float* __restrict__ v,
+                                                       float* __restrict__ y, int64_t rows, int64_t cols) {
+    const int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+    const float* m = M + row * cols;
+    double s = 0.0;
+    for (int64_t c = (threadIdx.x & 15) * 4; c < cols && row < rows; c += 64) {
+        if (c + 4 <= cols) s = fma4(*reinterpret_cast<const f4*>(m + c), *reinterpret_cast<const f4*>(v + c), s);
+        else
+            for (int64_t j = c; j < cols; ++j) s = __builtin_fma((double)m[j], (double)v[j], s);
+    }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if (row < rows && (threadIdx.x & 15) == 0) y[row] = (float)s;
+}
+
 // partial[chunk][j] = sum over the chunk's rows of v_i M[i][j]: 256 columns per block, four per
 // lane, a wave for every fourth row of the chunk
 __global__ __launch_bounds__(256) void mv_left_part(const float* __restrict__ M, const float* __restrict__ v,
-                                                    double* __restrict__ part, int64_t rows, int64_t cols,
-                                                    int64_t rows_per_chunk) {
+                                                    double* __restrict__ part, float* __restrict__ y, int64_t rows,
+                                                    int64_t cols, int64_t rows_per_chunk) {
     __shared__ double ws[3][256];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t j = (int64_t)blockIdx.x * 256 + lane * 4;
@@ -208,9 +243,11 @@ __global__ __launch_bounds__(256) void mv_left_part(const float* __restrict__ M,
     if (wave == 0)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            if (j + q < cols)
-                part[(int64_t)blockIdx.y * cols + j + q] =
-                    (acc[q] + ws[0][lane * 4 + q]) + (ws[1][lane * 4 + q] + ws[2][lane * 4 + q]);
+            if (j + q < cols) {
+                const double s = (acc[q] + ws[0][lane * 4 + q]) + (ws[1][lane * 4 + q] + ws[2][lane * 4 + q]);
+                if (y) y[j + q] = (float)s;  // a single chunk: nothing to add
+                else part[(int64_t)blockIdx.y * cols + j + q] = s;
+            }
 }
 
 // y = the chunks' sums: 32 columns per block, a thread for every eighth of the chunks (in order,
@@ -264,8 +301,11 @@ sg_status run_linalg(sg_ctx_s* ctx, sg_node_s* n, const FusedCheck* check) {
     n->count = n->n;
     if (n->binop == 0) {  // right: y = M v
         if (rows == 0) return SG_OK;
-        // a wave per row, four where that would leave CUs without a block
-        if (rows >= 4 * (int64_t)ctx->num_cu * 4)
+        // a wave per row, four where that would leave CUs without a block, a quarter for short rows
+        if (cols <= 512 && rows >= 16 * (int64_t)ctx->num_cu)
+            hipLaunchKernelGGL(mv_right_narrow, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, (const float*)M->dev,
+                               (const float*)v->dev, (float*)n->dev, rows, cols);
+        else if (rows >= 4 * (int64_t)ctx->num_cu * 4)
             hipLaunchKernelGGL(mv_right<1>, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, (const float*)M->dev,
                                (const float*)v->dev, (float*)n->dev, rows, cols);
         else
@@ -280,21 +320,22 @@ sg_status run_linalg(sg_ctx_s* ctx, sg_node_s* n, const FusedCheck* check) {
     const int64_t chunks = std::max<int64_t>(1, std::min<int64_t>((rows + 31) / 32, (2048 + cblocks - 1) / cblocks));
     const int64_t rpc = std::max<int64_t>(1, (rows + chunks - 1) / chunks);
     const int64_t nch = std::max<int64_t>(1, (rows + rpc - 1) / rpc);
-    double* part = (double*)dev_alloc(ctx, (size_t)nch * cols * sizeof(double));
-    if (!part) return fail(ctx, SG_E_OOM, "left_multiply: workspace");
+    float* y = rows > 0 && nch == 1 ? (float*)n->dev : nullptr;
+    double* part = y ? nullptr : (double*)dev_alloc(ctx, (size_t)nch * cols * sizeof(double));
+    if (!part && !y) return fail(ctx, SG_E_OOM, "left_multiply: workspace");
     if (rows > 0) {
         hipLaunchKernelGGL(mv_left_part, dim3((unsigned)cblocks, (unsigned)nch), dim3(256), 0, st, (const float*)M->dev,
-                           (const float*)v->dev, part, rows, cols, rpc);
+                           (const float*)v->dev, part, y, rows, cols, rpc);
     } else {
         (void)hipMemsetAsync(part, 0, (size_t)cols * sizeof(double), st);
     }
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) {
+    if (e == hipSuccess && !y) {
         hipLaunchKernelGGL(mv_left_sum, dim3((unsigned)((cols + 31) / 32)), dim3(256), 0, st, part, (float*)n->dev, cols,
                            rows > 0 ? nch : 1);
         e = hipGetLastError();
     }
-    dev_free(ctx, part);  // handed out again in stream order only
+    if (part) dev_free(ctx, part);  // handed out again in stream order only
     if (e != hipSuccess) return hip_fail(ctx, e, "left_multiply");
     return SG_OK;
 }

@@ -140,6 +140,13 @@ def test_matvec_row_and_column_edges(sg, ctx, rows, cols, offset):
         assert np.all(np.abs(got.astype(np.float64).ravel() - ex) <= 2.0 ** -24 * np.abs(ex) + 2.0 ** -40 * ab)
 
 
+@pytest.mark.parametrize("rows", [4095, 4096, 4111])
+@pytest.mark.parametrize("cols", [1, 3, 4, 5, 63, 64, 65, 511, 512, 513, 1027])
+def test_matvec_short_rows(sg, ctx, rows, cols):
+    """Rows of 16 lanes each, at the limits of that form and a last block cut short."""
+    test_matvec_row_and_column_edges(sg, ctx, rows, cols, 0)
+
+
 @pytest.mark.parametrize("rows,cols", [(64, 64), (128, 192), (130, 67), (257, 1028), (3, 5)])
 def test_checks_of_a_transposed_matrix(sg, ctx, rows, cols):
     """Class and range tests of a transpose, evaluated while it is made: the first failing index
