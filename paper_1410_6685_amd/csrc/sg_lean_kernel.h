@@ -14,7 +14,7 @@
 //
 // One sorted / all-finite check over 10^8 floats: 106 us (3.8 TB/s), before 202 / 172; the 2^20
 // chain with three clauses: 14 us, before 56; 256 chains of 2^10 .. 2^22 elements (786 MB) in
-// one batch at 256 x 4, 4 sub-tiles: 269 us (2.9 TB/s), before 535.  Bound by issue: with a
+// one batch at 256 x 4, 4 sub-tiles: 258 us (3.0 TB/s), before 535.  Bound by issue: with a
 // quarter of the elements per lane (unroll 1) the dispatch doubles the batch's time.
 //
 // Layout, accumulation order, publication and finalization are the streaming kernel's, so a
