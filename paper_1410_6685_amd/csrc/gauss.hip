@@ -28,7 +28,7 @@ constexpr int GR = 8;    // rows per update block
 
 struct DetState {
     int32_t sign;      // -1, 1; 0 once singular
-    int32_t singular;
+    int32_t singular;  // 0, or 1 + a column at or before the zero one (by panels: the panel's first)
     int64_t expo;      // det = sign * mant * 2^expo
     double mant;       // in [0.5, 1)
     int64_t piv;       // pivot row of the current column
@@ -378,7 +378,7 @@ __device__ __forceinline__ void panel(PanelLds<R, NB, MAXT>& S, const double* __
         int ww = __builtin_ctzll(vc);
         if (__builtin_expect(vmh == 0 || __builtin_popcountll(vc) != 1, 0)) ww = wave_pick(vkey, vpos);
         if (ww < 0) {  // the column is zero from here down: singular (the same for every wave)
-            if (tid == 0) st->singular = 1;
+            if (tid == 0) __hip_atomic_store(&st->singular, k0 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return;
         }
         const int32_t pp = __builtin_amdgcn_readlane(vpos, ww);
@@ -561,8 +561,11 @@ __global__ __launch_bounds__(MAXT) void g_step(double* __restrict__ W, const dou
         PanelLds<R, NB, MAXT> p;
         TrailLds<NB, TR, MAXT / 64> t;
     } S;
-    // set only by block 0, of this launch or an earlier one; the others' work is void then
-    if (__hip_atomic_load(&st->singular, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+    // Only an earlier launch's zero column ends a block here.  Block 0 of this one may find another
+    // meanwhile (its mark is k0 + NB + 1), and the waves of a block have to agree: one that left
+    // before the barriers would leave the others row numbers that nobody wrote.
+    const int32_t zero = __hip_atomic_load(&st->singular, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (zero != 0 && zero <= k0 + 1) return;
     const int b = (int)blockIdx.x;
     if (b == 0) {
         panel<R, NB, MAXT, true>(S.p, W, L, L1, n, k0 + NB, nb, rowmap, rowmap1, pivots, moved, st);

@@ -85,6 +85,21 @@ def test_det_singular_in_any_panel(sg, ctx, n, col):
     assert (s, np.isnan(m)) == (gauss_det(A)[0], np.isnan(gauss_det(A)[1]))
 
 
+@pytest.mark.parametrize("n,col", [(2000, 17), (2000, 31), (2048, 40), (1500, 32)])
+def test_det_singular_while_many_blocks_update(sg, ctx, n, col):
+    """The zero column is found while more blocks than fit the device bring the others up to date:
+    each of them has to decide by what earlier launches found.  Another node's determinant on the
+    same context stays right."""
+    say("gauss singular, many blocks", n, col)
+    A = np.triu(W.uniform_i32(n * n, 8, 1, 3).astype(np.float32).reshape(n, n))
+    A[col:, col] = 0.0
+    B = W.normal_f32(65 * 65, 65).reshape(65, 65)
+    for rep in range(3):
+        (s, m, e), _, _ = gpu_det(sg, ctx, A)
+        assert (s, m, e) == (0, 0.0, 0)
+        assert gpu_det(sg, ctx, B)[0] == gauss_det(B)[:3]
+
+
 @pytest.mark.parametrize("n", [1600, 2049, 2100])
 def test_det_of_a_permuted_triangular_matrix(sg, ctx, n):
     """Sizes whose first panels hold four rows per thread, and are narrower above 2048 rows: every
