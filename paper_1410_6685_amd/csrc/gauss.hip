@@ -194,6 +194,7 @@ __device__ __forceinline__ void lds_barrier() {
 // BEFORE: the panel's columns still lack the updates of the panel before it (multipliers Lb), which
 // are applied on the way into the registers: the pivot rows' own part by 16 lanes into LDS, then
 // every row: 5 to 8 us, half of it the reads of S.u (a broadcast takes as long as any LDS read).
+// rowmap and rowmap_out may be one array (g_panel): read at the start, written at the end.
 template <int R, int NB, int MAXT>
 struct PanelLds {
     double tile[MAXT / 64][64][NB + 1];
@@ -204,8 +205,8 @@ struct PanelLds {
 };
 template <int R, int NB, int MAXT, bool BEFORE>
 __device__ __forceinline__ void panel(PanelLds<R, NB, MAXT>& S, const double* __restrict__ W, const double* __restrict__ Lb,
-                                      double* __restrict__ L, int n, int k0, int nb, const int32_t* __restrict__ rowmap,
-                                      int32_t* __restrict__ rowmap_out, double* __restrict__ pivots,
+                                      double* __restrict__ L, int n, int k0, int nb, const int32_t* rowmap,
+                                      int32_t* rowmap_out, double* __restrict__ pivots,
                                       int32_t* __restrict__ moved, DetState* __restrict__ st) {
     auto& tile = S.tile;
     auto& prow = S.prow;
