@@ -422,7 +422,12 @@ __device__ __forceinline__ void flush_instance(const StreamArgs& A, LDS& L, kptr
                     if (k < nsum && q + j * B < nq)
                         s[k] += __builtin_bit_cast(double, ((x[j][2 + 2 * k] & 0xFFFFFFFFull) << 32) | (x[j][1 + 2 * k] & 0xFFFFFFFFull));
         }
-        if (late) atomicOr(&res->err, (uint32_t)ERR_FINALIZE_TIMEOUT);
+        if (late) {
+            atomicOr(&res->err, (uint32_t)ERR_FINALIZE_TIMEOUT);
+            // done before the barrier, which alone does not wait for it: the first thread reads the
+            // word behind it for the host
+            __builtin_amdgcn_s_waitcnt(0);
+        }
 #pragma unroll
         for (int k = 0; k < LDS::kSums; ++k)
             if (k < nsum) {
@@ -457,7 +462,7 @@ __device__ __forceinline__ void flush_instance(const StreamArgs& A, LDS& L, kptr
             }
         }
     }
-    // every block's error bits were set before its words were published
+    // every block's error bits were set before its words were published, this one's above
     if (INLINE && A.host && tid == 0)
         A.host->err = __hip_atomic_load(&res->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();

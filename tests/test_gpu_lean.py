@@ -107,3 +107,26 @@ def test_lean_check_finds_the_first_failing_element(sg, ctx, bad, pred, at):
     built = sg.build_spec(ctx, spec, to_dev({"x": x}))
     status, verdicts = built.program.execute()
     assert status == "post_violated" and verdicts[0].first_index == at
+
+
+@pytest.mark.parametrize("specialize", [False, True])
+@pytest.mark.parametrize("n", [100, 1 << 20, 4096 * SUB])
+def test_a_finalizer_that_gives_up_is_reported(sg, n, specialize):
+    """Results without a product check come to the host from the kernel itself, the error word with
+    them: a wait that gives up is an error of that execution, and the next one is clean."""
+    c = sg.Context(0)
+    c.set_specialize(specialize)
+    spec, inp = W.cfg1_spec(n), W.cfg1_inputs(n)
+    built = sg.build_spec(c, spec, to_dev(inp))
+    want = oracle.evaluate(spec, inp)
+    for rep in range(3):
+        c.set_wait_limit(0)
+        try:
+            say("lean forced wait failure", n, specialize, rep)
+            with pytest.raises(sg.SafeGPUError) as e:
+                built.program.execute()
+            assert e.value.status_name == "device"
+        finally:
+            c.set_wait_limit(-1)
+        status, verdicts = built.program.execute()
+        compare(spec, built, status, verdicts, want)
