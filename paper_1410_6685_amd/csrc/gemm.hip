@@ -98,10 +98,11 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
         }
         const auto rb = rsrc(B + (int64_t)k0 * N, (int64_t)(K - k0) * N);
         const uint32_t ka = (uint32_t)k0 * 4;
-        if (k0 + GBK <= ke && k0 + GBK < K) {
+        if (k0 + GBK <= ke && k0 + GBK + (N == 1 ? 3 : 1) <= K) {
             // whole slice: a row of A past M starts past the buffer's end, and what follows a
-            // row's end (columns of B past N) feeds columns of C that are not stored; the row of
-            // B behind the slice exists, so where 16 bytes straddle the buffer's end they hold
+            // row's end (columns of B past N) feeds columns of C that are not stored.  16 bytes that
+            // hold a stored column end at most three values into the row behind (one column: into
+            // the three rows behind), which exists, so those that straddle the buffer's end hold
             // nothing that is stored
 #pragma unroll
             for (int p = 0; p < P; ++p) {

@@ -54,6 +54,18 @@ def test_gemm_tiles_parts_and_tails(sg, ctx, M, K, N):
     assert np.all(np.abs(C[:-1, :-1].astype(np.float64) - C64[:-1, :-1]) <= bound[:-1, :-1])
 
 
+@pytest.mark.parametrize("M,K,N", [(64, k, n) for n in (1, 2, 3) for k in (33, 34, 35, 66)] +
+                         [(40_000, k, 1) for k in (17, 18, 19)])
+def test_gemm_few_columns_behind_a_whole_slice(sg, ctx, M, K, N):
+    """One to three rows of B behind the last whole slice of K, and rows shorter than 16 bytes: the
+    slice's last loads end at B's end.  Whole numbers, so the product is exact."""
+    say("gemm few columns", M, K, N)
+    g = np.random.default_rng(M + K + N)
+    A = g.integers(-8, 9, size=(M, K)).astype(np.float32)
+    B = g.integers(-8, 9, size=(K, N)).astype(np.float32)
+    assert np.array_equal(gemm(sg, ctx, A, B), (A.astype(np.int64) @ B.astype(np.int64)).astype(np.float32))
+
+
 @pytest.mark.parametrize("M,K,N", [(2048, 512, 1700), (1921, 513, 1793), (2050, 1000, 2047), (3713, 520, 3800)])
 def test_gemm_parts_of_values(sg, ctx, M, K, N):
     """The product on bfloat16 parts (tiles of 128 and 256, slices and rows that end anywhere):
