@@ -22,9 +22,9 @@ using namespace sg;
 
 hipError_t sg_launch_stream(const StreamArgs& a, int unroll, bool inl, bool lean, int grid, int block, size_t lds_bytes,
                             hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
-size_t sg_gemm_work_bytes(int64_t M, int64_t N, int64_t K, int num_cu);
+int sg_gemm_parts(int64_t M, int64_t N, int64_t K, int num_cu);
 hipError_t sg_launch_gemm_f32(const float* A, const float* B, float* C, int64_t M, int64_t N, int64_t K, int num_cu,
-                              void* work, hipStream_t s);
+                              float* work, hipStream_t s);
 hipError_t sg_launch_product_check(const float* C, const float* A, const float* B, const float* R, int64_t M,
                                    int64_t N, int64_t K, int64_t nvec, double tol, double* work, InstResult* res,
                                    hipStream_t s);
@@ -523,8 +523,9 @@ sg_status launch_program(sg_program_s* P, ExecSlot& es) {
             if ((st = alloc_output(ctx, C)) != SG_OK) return st;
             t_begin("gemm");
             const int64_t gm = step.A->rows, gn = step.B->cols, gk = step.A->cols;
-            const size_t wb = sg_gemm_work_bytes(gm, gn, gk, ctx->num_cu);
-            void* work = wb ? dev_alloc(ctx, wb) : nullptr;  // without it a slower kernel runs
+            const int parts = sg_gemm_parts(gm, gn, gk, ctx->num_cu);
+            // (at most two 64 x 64 tiles per CU; without it K stays in one part)
+            float* work = parts > 1 ? (float*)dev_alloc(ctx, (size_t)parts * gm * gn * 4) : nullptr;
             const hipError_t ge = sg_launch_gemm_f32((const float*)step.A->dev, (const float*)step.B->dev, (float*)C->dev, gm, gn,
                                                      gk, ctx->num_cu, work, ctx->stream);
             dev_free(ctx, work);  // reused in stream order only

@@ -103,6 +103,27 @@ def test_gemm_value_without_parts(sg, ctx, value, side):
     assert np.all(np.abs(C[ok] - C64[ok]) <= bound[ok])
 
 
+@pytest.mark.parametrize("M,K,N", [(200, 300, 130), (1000, 1531, 777), (2048, 512, 1700), (3713, 520, 3800)])
+@pytest.mark.parametrize("side", ["A", "B"])
+def test_gemm_single_products_are_rounded_once(sg, ctx, M, K, N, side):
+    """One nonzero entry per row of A (or column of B), of any value: each entry of the product is
+    one float32 product, rounded to nearest, at every size (no operand is shortened)."""
+    say("gemm single products", M, K, N, side)
+    A = W.normal_f32(M * K, 31).reshape(M, K)
+    B = W.normal_f32(K * N, 32).reshape(K, N)
+    if side == "A":
+        k, keep = np.arange(M) * 7 % K, np.zeros((M, K), bool)
+        keep[np.arange(M), k] = True
+        A[~keep] = 0
+        want = A[np.arange(M), k][:, None] * B[k]
+    else:
+        k, keep = np.arange(N) * 7 % K, np.zeros((K, N), bool)
+        keep[k, np.arange(N)] = True
+        B[~keep] = 0
+        want = A[:, k] * B[k, np.arange(N)][None]
+    assert np.array_equal(gemm(sg, ctx, A, B), want)
+
+
 def test_gemm_empty_inner_dimension(sg, ctx):
     import torch
     c = ctx.wrap(torch.zeros((5, 0), device="cuda")).matmul(ctx.wrap(torch.zeros((0, 7), device="cuda")))
