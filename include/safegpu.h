@@ -252,11 +252,10 @@ sg_status sg_matvec(sg_node M, sg_node v, int side, sg_node* out);
 sg_status sg_concat(sg_node a, sg_node b, sg_node* out);
 /* The quicksort of Section 4 (Listing 3) on an f32 or i32 vector: pivot = the item at index
  * count / 2, three stable filters (less, equal, greater), result = quicksort(less) ++ equal ++
- * quicksort(greater).  Without NaN that is the stable sort of the input, computed by digit
- * passes; otherwise the recursion runs level by level on the GPU.  Items no filter keeps (NaN items, or all
- * items of a collection whose pivot is NaN) are dropped, as in the listing, so the result's
- * count can be smaller than the input's: attach sg_program_count_eq to check it.  Capacity =
- * the input's capacity. */
+ * quicksort(greater).  Without NaN that is the stable sort of the input.  Items no filter keeps
+ * (NaN items, or all items of a collection whose pivot is NaN) are dropped, as in the listing, so
+ * the result's count can be smaller than the input's: attach sg_program_count_eq to check it.
+ * Capacity = the input's capacity. */
 sg_status sg_quicksort(sg_node in, sg_node* out);
 /* Determinant of a square f32 matrix by Gaussian elimination (Section 5, Listing 5, in its
  * textbook form: partial pivoting, a zero pivot column means det = 0), in float64 on the

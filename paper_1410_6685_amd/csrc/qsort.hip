@@ -12,9 +12,9 @@
 // is never NaN), so the result is the listing's concatenation and its count is what the
 // postcondition count = old count compares.
 //
-// More than 2048 items without a NaN never get here: their result is the stable sort, which
-// radix.hip computes in a few passes (10^8 float32: 1.7 ms against 13.9 ms by levels).  The
-// levels below run for inputs holding a NaN, the leaves also for up to 2048 items.
+// More than 2048 items are sorted by radix.hip, which computes the listing's result in a few
+// passes (10^8 float32: 1.6 ms against 13.9 ms by levels).  The levels below run from 2^32 items,
+// the leaves for up to 2048.
 //
 // Large segments are partitioned by three kernels per level over 4096-item tiles: count the
 // four classes per tile, scan the tile counts per segment, then scatter (LDS-staged, so that
@@ -484,7 +484,7 @@ using namespace sgrt;
 
 namespace sgrt {
 
-sg_status radix_sort(sg_ctx_s* ctx, const uint32_t* src, uint32_t* dst, int64_t m, bool is_f32, bool* done);
+sg_status radix_sort(sg_ctx_s* ctx, const uint32_t* src, uint32_t* dst, int64_t m, bool is_f32, int64_t* count);
 
 // Sort the `m` items at `in` into `out` (capacity >= m); returns the count of the result (m
 // minus the dropped items) in *count.  Work buffers come from the context's pool.
@@ -500,11 +500,7 @@ sg_status run_quicksort(sg_ctx_s* ctx, const void* in, void* out, int64_t m, boo
         SG_HIP(ctx, hipGetLastError());
         return SG_OK;
     }
-    if (m > QLEAF_N && m <= (int64_t)0xFFFFFFFF) {
-        bool sorted = false;
-        const sg_status s = radix_sort(ctx, src, dst, m, is_f32, &sorted);
-        if (s != SG_OK || sorted) return s;
-    }
+    if (m > QLEAF_N && m <= (int64_t)0xFFFFFFFF) return radix_sort(ctx, src, dst, m, is_f32, count);
     const int64_t max_tiles = (m + QTE - 1) / QTE + (m + QLEAF_N) / (QLEAF_N + 1) + 2;
     const int64_t max_segs = m / (QLEAF_N + 1) + 2;
     const int64_t max_leaves = m / 2 + 2;

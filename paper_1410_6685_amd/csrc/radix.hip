@@ -1,10 +1,15 @@
-// Sort of items without NaN by digits of their order-preserving keys.
+// Sort of items by digits of their order-preserving keys.
 //
 // Without NaN every filter of the quicksort of Section 4 (Listing 3) keeps each item on one
 // side of every pivot, and items that compare equal (-0 and +0 included) stay together in
 // input order, so the listing's result is the stable sort of the input, whatever the pivots.
 // A least-significant-digit radix sort computes that sort in at most four passes over the
 // data where the recursion takes about 2 log2(n / 2048) levels.
+//
+// No filter keeps a NaN.  So the first pivot decides: if it is a NaN, the three filters are empty
+// and so is the result; if not, every NaN is gone after the first level and the result is the
+// stable sort of the others.  The passes then give NaN the largest key (which no number has), and
+// the result ends before them.
 //
 // The items keep their bits (a -0 stays a -0); a pass extracts its 8-bit digit from the key:
 // int32 by value, float32 by value with both zeros one key.  Keys are taken relative to the
@@ -34,23 +39,30 @@ constexpr int RCOPY = 16;         // copies of a digit's counter in r_hist
 
 struct KeyInfo {
     uint32_t min, max;  // of the keys
-    uint32_t nan;       // 1: an item is a NaN
-    uint32_t pad;
+    uint32_t nan;       // items that are NaN
+    uint32_t pivot;     // 1: the listing's first pivot is one
 };
 
+enum Kind { INT, FLT, NANS };  // int32, float32 without NaN, float32
+
+__device__ __forceinline__ bool is_nan(uint32_t u) { return (u & 0x7FFFFFFFu) > 0x7F800000u; }
+
 // Order-preserving unsigned key.  x + 0 maps -0 to +0 and leaves every other number as it is.
-template <bool F>
+// (NaN keys take two instructions more per item, so only inputs with a NaN scatter by them.)
+template <Kind F>
 __device__ __forceinline__ uint32_t rkey(uint32_t u) {
-    if (!F) return u ^ 0x80000000u;
+    if (F == INT) return u ^ 0x80000000u;
+    const bool nan = F == NANS && is_nan(u);
     u = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, u) + 0.0f);
-    return u ^ (uint32_t)(((int32_t)u >> 31) | (int32_t)0x80000000);
+    u ^= (uint32_t)(((int32_t)u >> 31) | (int32_t)0x80000000);
+    return nan ? ~0u : u;
 }
 
-// Digit counts of one chunk (cnt[digit][chunk]); FIRST: also the keys' range and whether any
-// item is a NaN.  Bound by the read.  A digit has 16 counters, one per lane modulo 16, so that
+// Digit counts of one chunk (cnt[digit][chunk]); FIRST: also the keys' range and how many
+// items are NaN.  Bound by the read.  A digit has 16 counters, one per lane modulo 16, so that
 // equal digits (the exponent byte of ordinary floats has a handful of values) serialize at most
 // four lanes of an LDS atomic.
-template <bool F, bool FIRST>
+template <Kind F, bool FIRST>
 __global__ __launch_bounds__(RB) void r_hist(const uint32_t* __restrict__ a, int64_t n, int64_t chunk, uint32_t bias,
                                              int shift, uint32_t* __restrict__ cnt, KeyInfo* __restrict__ info) {
     __shared__ uint32_t h[RD * RCOPY];
@@ -60,13 +72,14 @@ __global__ __launch_bounds__(RB) void r_hist(const uint32_t* __restrict__ a, int
     __syncthreads();
     const int64_t lo = (int64_t)blockIdx.x * chunk, hi = std::min<int64_t>(lo + chunk, n);
     const int c = tid & (RCOPY - 1);
+    if (FIRST && F != INT && tid == 0 && n / 2 >= lo && n / 2 < hi && is_nan(a[n / 2])) info->pivot = 1u;
     uint32_t kmin = ~0u, kmax = 0u, nan = 0u;
     auto take = [&](uint32_t u) {
         const uint32_t k = rkey<F>(u);
         if (FIRST) {
             kmin = min(kmin, k);
             kmax = max(kmax, k);
-            if (F) nan |= (u & 0x7FFFFFFFu) > 0x7F800000u;
+            if (F != INT) nan += is_nan(u) ? 1u : 0u;
         }
         atomicAdd(&h[(((k - bias) >> shift) & (RD - 1)) * RCOPY + c], 1u);
     };
@@ -102,7 +115,7 @@ __global__ __launch_bounds__(RB) void r_hist(const uint32_t* __restrict__ a, int
         for (int o = 32; o > 0; o >>= 1) {
             kmin = min(kmin, (uint32_t)__shfl_xor(kmin, o));
             kmax = max(kmax, (uint32_t)__shfl_xor(kmax, o));
-            nan |= __shfl_xor(nan, o);
+            nan += __shfl_xor(nan, o);
         }
         if ((tid & 63) == 0) {
             smin[tid >> 6] = kmin;
@@ -121,11 +134,11 @@ __global__ __launch_bounds__(RB) void r_hist(const uint32_t* __restrict__ a, int
         for (int w = 1; w < RW; ++w) {
             kmin = min(kmin, smin[w]);
             kmax = max(kmax, smax[w]);
-            nan |= snan[w];
+            nan += snan[w];
         }
         atomicMin(&info->min, kmin);
         atomicMax(&info->max, kmax);
-        if (nan) atomicOr(&info->nan, 1u);
+        if (nan) atomicAdd(&info->nan, nan);
     }
 }
 
@@ -174,7 +187,7 @@ __global__ __launch_bounds__(256) void r_scan(uint32_t* __restrict__ cnt, uint32
 // conditions, and LDS reads go in batches: 296 -> 246 us.  Finding equal digits by atomic ORs of
 // lane masks in LDS is no faster on spread digits and half as fast on equal ones; loading the
 // next tile ahead spills.
-template <bool F, int I>
+template <Kind F, int I>
 __global__ __launch_bounds__(RB, I == 4 ? 2 : 4) void r_scatter(const uint32_t* __restrict__ a, uint32_t* __restrict__ out,
                                                                int64_t n, int64_t chunk, uint32_t bias, int shift,
                                                                const uint32_t* __restrict__ cnt,
@@ -299,12 +312,9 @@ __global__ void r_info_init(KeyInfo* info) { *info = KeyInfo{~0u, 0u, 0u, 0u}; }
 
 namespace sgrt {
 
-// Stable sort of m items (2 <= m < 2^32) from src to dst when none is a NaN: *done = true.  An
-// input holding a NaN is left alone (*done = false): the listing's recursion decides what
-// becomes of it.
-sg_status radix_sort(sg_ctx_s* ctx, const uint32_t* src, uint32_t* dst, int64_t m, bool is_f32, bool* done) {
+// The quicksort of m items (2 <= m < 2^32) from src to dst; *count of them are in the result.
+sg_status radix_sort(sg_ctx_s* ctx, const uint32_t* src, uint32_t* dst, int64_t m, bool is_f32, int64_t* count) {
     using namespace sgr;
-    *done = false;
     hipStream_t st = ctx->stream;
     const bool small = m < (int64_t)ctx->num_cu * RB * 16;
     const int64_t tile = small ? RB * 4 : RB * 16;
@@ -322,44 +332,57 @@ sg_status radix_sort(sg_ctx_s* ctx, const uint32_t* src, uint32_t* dst, int64_t 
     KeyInfo* info = (KeyInfo*)(w + b_items + b_cnt + b_tot);
     KeyInfo h{};
     hipError_t e = hipSuccess;
-    auto hist = [&](const uint32_t* from, uint32_t bias, int shift, bool first) {
-        const dim3 g((unsigned)chunks), b(RB);
-        if (first && is_f32) hipLaunchKernelGGL((r_hist<true, true>), g, b, 0, st, from, m, chunk, bias, shift, cnt, info);
-        else if (first) hipLaunchKernelGGL((r_hist<false, true>), g, b, 0, st, from, m, chunk, bias, shift, cnt, info);
-        else if (is_f32) hipLaunchKernelGGL((r_hist<true, false>), g, b, 0, st, from, m, chunk, bias, shift, cnt, info);
-        else hipLaunchKernelGGL((r_hist<false, false>), g, b, 0, st, from, m, chunk, bias, shift, cnt, info);
+    const dim3 g((unsigned)chunks), b(RB);
+#define SGR_HIST(F, FIRST) hipLaunchKernelGGL((r_hist<F, FIRST>), g, b, 0, st, from, m, chunk, bias, shift, cnt, info)
+#define SGR_SCATTER(F, I) hipLaunchKernelGGL((r_scatter<F, I>), g, b, 0, st, from, to, m, chunk, bias, shift, cnt, tot)
+    auto first_hist = [&](const uint32_t* from, uint32_t bias, int shift) {
+        if (is_f32) SGR_HIST(NANS, true);
+        else SGR_HIST(INT, true);
     };
     // the first count is taken before the keys' range is known; the range's lower end is cut to
     // a multiple of 256, so the lowest digit is the same with and without it
     hipLaunchKernelGGL(r_info_init, dim3(1), dim3(1), 0, st, info);
-    hist(src, 0u, 0, true);
+    first_hist(src, 0u, 0);
     if (e == hipSuccess) e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpyAsync(&h, info, sizeof(h), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess || h.nan) {
+    if (e != hipSuccess || h.pivot) {
         dev_free(ctx, w);
+        *count = 0;
         return e != hipSuccess ? hip_fail(ctx, e, "quicksort: digit count") : SG_OK;
     }
+    const Kind kind = !is_f32 ? INT : h.nan ? NANS : FLT;
     const uint32_t bias = h.min & ~(uint32_t)(RD - 1), range = h.max - bias;
     int passes = 1;
     while (passes < 4 && (range >> (8 * passes)) != 0) ++passes;
     const uint32_t* from = src;
     for (int p = 0; p < passes && e == hipSuccess; ++p) {
         uint32_t* to = (passes - 1 - p) % 2 == 0 ? dst : tmp;
-        if (p > 0) hist(from, bias, 8 * p, false);
+        const int shift = 8 * p;
+        if (p > 0) {
+            if (kind == INT) SGR_HIST(INT, false);
+            else if (kind == FLT) SGR_HIST(FLT, false);
+            else SGR_HIST(NANS, false);
+        }
         hipLaunchKernelGGL(r_scan, dim3(RD), dim3(256), 0, st, cnt, tot, chunks);
-        const dim3 g((unsigned)chunks), b(RB);
-        if (is_f32 && small) hipLaunchKernelGGL((r_scatter<true, 4>), g, b, 0, st, from, to, m, chunk, bias, 8 * p, cnt, tot);
-        else if (is_f32) hipLaunchKernelGGL((r_scatter<true, 16>), g, b, 0, st, from, to, m, chunk, bias, 8 * p, cnt, tot);
-        else if (small) hipLaunchKernelGGL((r_scatter<false, 4>), g, b, 0, st, from, to, m, chunk, bias, 8 * p, cnt, tot);
-        else hipLaunchKernelGGL((r_scatter<false, 16>), g, b, 0, st, from, to, m, chunk, bias, 8 * p, cnt, tot);
+        if (small) {
+            if (kind == INT) SGR_SCATTER(INT, 4);
+            else if (kind == FLT) SGR_SCATTER(FLT, 4);
+            else SGR_SCATTER(NANS, 4);
+        } else {
+            if (kind == INT) SGR_SCATTER(INT, 16);
+            else if (kind == FLT) SGR_SCATTER(FLT, 16);
+            else SGR_SCATTER(NANS, 16);
+        }
         e = hipGetLastError();
         from = to;
     }
+#undef SGR_SCATTER
+#undef SGR_HIST
     // the pool hands the block out again in stream order only
     dev_free(ctx, w);
     if (e != hipSuccess) return hip_fail(ctx, e, "quicksort: digit pass");
-    *done = true;
+    *count = m - h.nan;
     return SG_OK;
 }
 

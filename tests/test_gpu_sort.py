@@ -71,6 +71,35 @@ def test_quicksort_drops_nan_like_the_listing(sg, ctx, n):
     compare(spec, built, status, verdicts, ref)
 
 
+@pytest.mark.parametrize("n", [2049, 50_000, 2_097_151, 2_097_153])
+@pytest.mark.parametrize("kind", ["one", "most", "pivot", "all but the pivot"])
+def test_digit_sort_with_nan(sg, ctx, n, kind):
+    """The first pivot (the item at index n / 2) decides: a NaN there leaves nothing, else the
+    result is the stable sort of the items that are not NaN, whatever their signs and payloads."""
+    say("digit sort with NaN", n, kind)
+    x = W.normal_f32(n, 7)
+    x[::11] = np.inf
+    x[1::11] = -np.inf
+    x[2::11] = 0.0
+    x[3::11] = -0.0
+    nans = np.array([0x7FC00000, 0xFFC00000, 0x7F800001, 0xFFFFFFFF, 0x7FFFFFFF], np.uint32).view(np.float32)
+    at = {"one": np.array([n - 1]), "most": np.arange(n)[np.arange(n) % 10 != 0], "pivot": np.array([n // 2]),
+          "all but the pivot": np.arange(n)}[kind]
+    if kind != "pivot":
+        at = at[at != n // 2]
+    x[at] = nans[np.arange(at.size) % nans.size]
+    built = sg.build_spec(ctx, qs_spec(n), to_dev({"a": x}))
+    status, verdicts = built.program.execute()
+    keep = x[~np.isnan(x)] if kind != "pivot" else x[:0]
+    want = np.sort(keep, kind="stable")
+    if n < 10_000:
+        assert np.array_equal(oracle.quicksort(x).view(np.uint32), want.view(np.uint32))
+    assert status == "post_violated" and verdicts[0].holds == 1
+    assert verdicts[1].holds == 0 and verdicts[1].measure == want.size - n
+    got = built["r"].to_host()
+    assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
+
+
 def test_quicksort_nan_pivot_hand_cases(sg, ctx):
     for x, want in [([np.nan, 1, 2], [1, 2]), ([1, np.nan, 2], []), ([2, 1, 3, np.nan], [1, 2, 3]),
                     ([3, 1, np.nan, 2], [])]:
