@@ -151,9 +151,9 @@ static_assert(TT / 64 == TSW && TG == 16, "a wave per sample, 4 x 4 parameter bl
 struct MlpShared {
     float h1[MB][MH], h2[MB][MH], d2[MB][MH], d1[MB][MH];
     float dy[MB], loss[MB];
-    uint64_t arrived;  // workgroups that reached a barrier, over the whole launch
-    uint64_t failed;   // 1: a barrier timed out
+    uint64_t arrived;  // workgroups that reached a barrier, over the whole launch; or GIVEN_UP
 };
+constexpr uint64_t GIVEN_UP = 1ull << 63;
 
 __device__ __forceinline__ uint64_t xld(const void* p) {
     return __hip_atomic_load((const uint64_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -165,11 +165,33 @@ __device__ __forceinline__ void xst(float* p, float v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Train for `epochs` passes over n samples in batches of B (the last partial batch included).
+// a + x[0] w[0] + x[1] w[WS] + ..., MH terms in order.  The LDS reads of 16 terms are issued together:
+// left to itself the compiler may wait for each pair (its choice hangs on unrelated code; a step
+// then takes 1.3 us more).
+template <int WS>
+__device__ __forceinline__ float dot_mh(float a, const float* x, const float* w) {
+#pragma unroll 1
+    for (int i = 0; i < MH; i += 16) {
+        float xv[16], wv[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            xv[q] = x[i + q];
+            wv[q] = w[(i + q) * WS];
+        }
+#pragma unroll
+        for (int q = 0; q < 16; ++q) a += xv[q] * wv[q];
+        __builtin_amdgcn_sched_group_barrier(0x100, 16, 0);  // the reads,
+        __builtin_amdgcn_sched_group_barrier(0x002, 40, 0);  // then the arithmetic
+    }
+    return a;
+}
+
+// Train for `epochs` passes over n samples in batches of B (the last partial batch included).  The
+// parameters at the start are kept behind P (the place of a gradient call's result).
 __global__ __launch_bounds__(TT) void mlp_train_kernel(float* __restrict__ P, float* __restrict__ M1, float* __restrict__ M2,
                                                        const float* __restrict__ X, const float* __restrict__ T, int64_t n,
                                                        int B, int epochs, int step0, AdamArgs ad,
-                                                       double* __restrict__ epoch_loss, MlpShared* ex) {
+                                                       double* __restrict__ epoch_loss, MlpShared* ex, uint32_t limit) {
     __shared__ float w1[MI * MH], w2[MH * W2P], b1[MH], b2[MH], w3[MH], b3[1];
     __shared__ float sx[TSW][MI], sh1[TSW][MH], sh2[TSW][MH], sd2[TSW][MH];
     __shared__ float ch1[MB][TC], cd2[MB][TC], cd1[MB][TC], ch2[MB][TC], cx[MB][TI], cdy[MB], closs[MB], one[1];
@@ -199,28 +221,34 @@ __global__ __launch_bounds__(TT) void mlp_train_kernel(float* __restrict__ P, fl
         else if (g == 3 * 4 && j == 0) own = OB3;
     }
     float p = 0.f, m1 = 0.f, m2 = 0.f;
-    if (own >= 0) { p = P[own]; m1 = M1[own]; m2 = M2[own]; }
+    if (own >= 0) { p = P[own]; m1 = M1[own]; m2 = M2[own]; P[MP + own] = p; }
     if (tid == 0) one[0] = 1.f;
     uint64_t target = 0;
-    // every workgroup's stores so far are in memory before any workgroup passes
+    // Every workgroup's stores so far are in memory before any workgroup passes.  The wait is bounded
+    // (`limit` polls, seconds).  A workgroup gives up by marking the counter, and only while the
+    // count is short, so the others read either the full count or the mark: all of them pass the
+    // last barrier or none does.  Where none does, the host puts the parameters back (the moments
+    // are written after the last barrier).
     auto barrier = [&]() -> bool {
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         target += TG;
         if (tid == 0) {
             (void)__hip_atomic_fetch_add(&ex->arrived, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            int ok = 1;
-            // bounded (seconds): a workgroup that gives up lets the others give up too
-            for (uint32_t spins = 0; xld(&ex->arrived) < target; ++spins)
-                if (spins >= (1u << 22)) {
-                    __hip_atomic_store(&ex->failed, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    ok = 0;
-                    break;
-                }
-            go = ok;
+            // (v stays the same for the whole wave to the compiler: a scalar loop)
+            uint64_t v = xld(&ex->arrived);
+            for (uint32_t spins = 1; v < target && spins < limit; ++spins) v = xld(&ex->arrived);
+            if (__builtin_expect(v < target, 0)) do {
+                uint64_t seen = v;
+                const bool marked = __hip_atomic_compare_exchange_strong(&ex->arrived, &seen, v | GIVEN_UP, __ATOMIC_RELAXED,
+                                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                // (one that fails saw an arrival, of which there are at most TG)
+                v = __builtin_amdgcn_readfirstlane(marked) ? GIVEN_UP : xld(&ex->arrived);
+            } while (v < target);
+            go = v < GIVEN_UP;
         }
         __syncthreads();
-        return go != 0;
+        return __builtin_amdgcn_readfirstlane(go) != 0;
     };
     int step = step0;
     for (int e = 0; e < epochs; ++e) {
@@ -266,9 +294,7 @@ __global__ __launch_bounds__(TT) void mlp_train_kernel(float* __restrict__ P, fl
                 const float h1 = a > 0.f ? a : 0.f;
                 sh1[wave][j] = h1;
                 __builtin_amdgcn_wave_barrier();  // one wave's LDS accesses keep their order
-                a = b2[j];
-#pragma unroll 16
-                for (int i = 0; i < MH; ++i) a += sh1[wave][i] * w2[i * W2P + j];
+                a = dot_mh<W2P>(b2[j], sh1[wave], w2 + j);
                 const float h2 = a > 0.f ? a : 0.f;
                 sh2[wave][j] = h2 * w3[j];
                 __builtin_amdgcn_wave_barrier();
@@ -280,9 +306,7 @@ __global__ __launch_bounds__(TT) void mlp_train_kernel(float* __restrict__ P, fl
                 const float d2 = h2 > 0.f ? dy * w3[j] : 0.f;
                 sd2[wave][j] = d2;
                 __builtin_amdgcn_wave_barrier();
-                a = 0.f;
-#pragma unroll 16
-                for (int i = 0; i < MH; ++i) a += sd2[wave][i] * w2[j * W2P + i];
+                a = dot_mh<1>(0.f, sd2[wave], w2 + j * W2P);
                 const float d1 = h1 > 0.f ? a : 0.f;
                 xst(&ex->h1[s][j], h1);
                 xst(&ex->h2[s][j], h2);
@@ -496,30 +520,40 @@ sg_status sg_mlp_train(sg_mlp m, const float* X_dev, const float* T_dev, int64_t
     sg::AdamArgs ad{lr, 0.9f, 0.999f, 1e-8f};
     const char* name = "mlp_train";
     auto* ex = (sg::MlpShared*)m->shared;
-    SG_HIP(ctx, hipMemsetAsync(&ex->arrived, 0, 2 * sizeof(uint64_t), ctx->stream));
-    hipEvent_t a = nullptr, b = nullptr;
-    if (ctx->timing) {
-        (void)hipEventCreate(&a);
-        (void)hipEventCreate(&b);
-        (void)hipEventRecord(a, ctx->stream);
-    }
-    hipLaunchKernelGGL(sg::mlp_train_kernel, dim3(sg::TG), dim3(sg::TT), 0, ctx->stream, m->P, m->P + 2 * sg::MP,
-                       m->P + 3 * sg::MP, X_dev, T_dev, n, (int)batch, (int)epochs, m->step, ad, m->loss, ex);
-    SG_HIP(ctx, hipGetLastError());
-    if (ctx->timing) (void)hipEventRecord(b, ctx->stream);
-    m->step += (int)(epochs * ((n + batch - 1) / batch));
+    const uint32_t limit = ctx->wait_limit ? ctx->wait_limit - 1u : sg::kDefaultWaitSpins;
     std::vector<double> el(epochs);
-    uint64_t failed = 0;
-    SG_HIP(ctx, hipMemcpyAsync(el.data(), m->loss, epochs * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-    SG_HIP(ctx, hipMemcpyAsync(&failed, &ex->failed, sizeof(failed), hipMemcpyDeviceToHost, ctx->stream));
-    SG_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    if (ctx->timing) {
-        float ms = 0.f;
-        if (hipEventElapsedTime(&ms, a, b) == hipSuccess) { ctx->times[name].ms += ms; ctx->times[name].n += 1; }
-        (void)hipEventDestroy(a);
-        (void)hipEventDestroy(b);
+    // The training workgroups have to be on the device together.  While other work holds it their
+    // wait can end, with the model as it was, and the training is launched again; with a limit set by
+    // the caller the first such end is reported.
+    uint64_t arrived = sg::GIVEN_UP;
+    for (int tries = 0; arrived >= sg::GIVEN_UP && tries < (ctx->wait_limit ? 1 : 8); ++tries) {
+        // (a limit of no polls: given up before the first barrier)
+        SG_HIP(ctx, hipMemsetAsync(&ex->arrived, limit ? 0 : 0x80, sizeof(uint64_t), ctx->stream));
+        hipEvent_t a = nullptr, b = nullptr;
+        if (ctx->timing) {
+            (void)hipEventCreate(&a);
+            (void)hipEventCreate(&b);
+            (void)hipEventRecord(a, ctx->stream);
+        }
+        hipLaunchKernelGGL(sg::mlp_train_kernel, dim3(sg::TG), dim3(sg::TT), 0, ctx->stream, m->P, m->P + 2 * sg::MP,
+                           m->P + 3 * sg::MP, X_dev, T_dev, n, (int)batch, (int)epochs, m->step, ad, m->loss, ex, limit);
+        SG_HIP(ctx, hipGetLastError());
+        if (ctx->timing) (void)hipEventRecord(b, ctx->stream);
+        SG_HIP(ctx, hipMemcpyAsync(el.data(), m->loss, epochs * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+        SG_HIP(ctx, hipMemcpyAsync(&arrived, &ex->arrived, sizeof(arrived), hipMemcpyDeviceToHost, ctx->stream));
+        SG_HIP(ctx, hipStreamSynchronize(ctx->stream));
+        if (arrived >= sg::GIVEN_UP)
+            SG_HIP(ctx, hipMemcpyAsync(m->P, m->P + sg::MP, sg::MP * sizeof(float), hipMemcpyDeviceToDevice, ctx->stream));
+        if (ctx->timing) {
+            float ms = 0.f;
+            if (hipEventElapsedTime(&ms, a, b) == hipSuccess) { ctx->times[name].ms += ms; ctx->times[name].n += 1; }
+            (void)hipEventDestroy(a);
+            (void)hipEventDestroy(b);
+        }
     }
-    if (failed) return fail(ctx, SG_E_DEVICE, "mlp_train: a barrier of the training workgroups timed out");
+    if (arrived >= sg::GIVEN_UP)
+        return fail(ctx, SG_E_DEVICE, "mlp_train: a barrier of the training workgroups timed out; the model is unchanged");
+    m->step += (int)(epochs * ((n + batch - 1) / batch));
     if (epoch_loss) std::memcpy(epoch_loss, el.data(), epochs * sizeof(double));
     return SG_OK;
 }

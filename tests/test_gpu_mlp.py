@@ -67,6 +67,36 @@ def test_training_batches_that_do_not_fill_the_workgroups(sg, ctx, n, batch):
     assert np.array_equal(twice.params().view(np.uint32), p.view(np.uint32))
 
 
+@pytest.mark.parametrize("limit", [0, 1, 2, 4, 8, 32])
+def test_a_training_that_gives_up_leaves_the_model(sg, limit):
+    """A barrier of the training workgroups that gives up (after the host's wait limit: at once, or
+    at whatever barrier takes longer) is a device error; parameters, moments and step count stay,
+    so the next trainings give the bits of a model that was never disturbed."""
+    c = sg.Context(0)
+    X, T = W.mlp_synthetic_dataset(700, 3)
+    t = to_dev({"X": X, "T": T})
+    p0 = W.mlp_init_params(4)
+    net, plain = sg.Mlp(c, p0), sg.Mlp(c, p0)
+    for rep in range(4):
+        want = plain.train(t["X"], t["T"], batch=64, epochs=2)
+        before = net.params()
+        got = None
+        c.set_wait_limit(limit)
+        try:
+            say("mlp wait limit", limit, rep)
+            got = net.train(t["X"], t["T"], batch=64, epochs=2)
+        except sg.SafeGPUError as e:
+            assert e.status_name == "device"
+            assert np.array_equal(net.params().view(np.uint32), before.view(np.uint32))
+        finally:
+            c.set_wait_limit(-1)
+        assert limit > 0 or got is None
+        if got is None:
+            got = net.train(t["X"], t["T"], batch=64, epochs=2)
+        assert np.array_equal(got, want)
+        assert np.array_equal(net.params().view(np.uint32), plain.params().view(np.uint32))
+
+
 def test_predict_matches_oracle(sg, ctx):
     X, _ = W.mlp_synthetic_dataset(1000, 8)
     p0 = W.mlp_init_params(9)
