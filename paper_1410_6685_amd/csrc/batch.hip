@@ -86,7 +86,6 @@ sg_status sg_batch_create(sg_ctx ctx, const sg_program* progs, int32_t n, int us
         max_sums = std::max(max_sums, ip.nsum);
         max_cemit = std::max(max_cemit, inst_cemit(ip));
         any_scan |= ip.scan_space != 0;
-        ip.lean = lean_program(ip);
         b->lean = (i == 0 || b->lean) && !ip.lean.empty();
     }
     b->lean &= b->block <= LEAN_BLOCK;

@@ -128,6 +128,11 @@ std::vector<SgOp> lean_program(const InstPlan& ip) {
     return out;
 }
 
+PassRows pass_rows(const sg_ctx_s* ctx, const InstPlan& ip, int block) {
+    const bool lean = !ctx->specialize && !ip.lean.empty() && block <= LEAN_BLOCK;
+    return {lean, ctx->specialize ? 0 : (int)ip.slot_kind.size(), ctx->specialize || lean ? 0 : ip.nsum};
+}
+
 void set_lean(InstDesc& d, const std::vector<SgOp>& lean) {
     d.prog_len = (int32_t)lean.size();
     for (const SgOp& o : lean)
@@ -347,7 +352,6 @@ sg_status launch_program(sg_program_s* P, ExecSlot& es) {
     if (!P->plan.valid || P->plan.generation != ctx->generation) {
         sg_status st = build_plan(P, &P->plan);
         if (st != SG_OK) { P->plan.valid = false; return st; }
-        for (auto& ip : P->plan.insts) ip.lean = lean_program(ip);
     }
     Plan& plan = P->plan;
     const int block = P->block ? P->block : ctx->block;
@@ -363,11 +367,9 @@ sg_status launch_program(sg_program_s* P, ExecSlot& es) {
     for (size_t i = 0; i < plan.insts.size(); ++i) {
         const InstPlan& ip = plan.insts[i];
         Geo& g = geo[i];
-        // a specialized kernel keeps its accumulators in registers: no LDS rows for them
-        g.lean = !ctx->specialize && !ip.lean.empty() && block <= LEAN_BLOCK;
-        // (a lean one its sums)
-        const int ns = ctx->specialize ? 0 : (int)ip.slot_kind.size(), nu = ctx->specialize || g.lean ? 0 : ip.nsum;
-        const int ce = inst_cemit(ip);
+        const PassRows rows = pass_rows(ctx, ip, block);
+        g.lean = rows.lean;
+        const int ns = rows.slots, nu = rows.sums, ce = inst_cemit(ip);
         for (g.U = unroll;; g.U /= 2) {
             // without a plan, a short vector's tiles are cut until every CU has two (n = 2^20: 64 tiles
             // of 8 sub-tiles or 512 of one), the lean kernel's, of which more blocks fit a CU, until

@@ -684,6 +684,7 @@ sg_status build_plan(sg_program_s* P, Plan* plan) {
             if (!progress) return fail(ctx, SG_E_INVALID, "planner: cyclic dependency");
         }
         plan->mats.assign(mat.begin(), mat.end());
+        for (auto& ip : plan->insts) ip.lean = lean_program(ip);
         plan->valid = true;
         return SG_OK;
     }

@@ -243,6 +243,13 @@ int coresident_blocks(int occupancy, int lds_blocks, bool waits_on_others);
 // A pass's program in the lean interpreter's form (its checks fused), or empty when it needs the
 // general one.
 std::vector<sg::SgOp> lean_program(const InstPlan& ip);
+// The interpreter that a pass runs on alone, at this block size, and its LDS rows: none for a
+// specialized kernel's accumulators, which stay in registers, nor for a lean one's sums.
+struct PassRows {
+    bool lean;
+    int slots, sums;
+};
+PassRows pass_rows(const sg_ctx_s* ctx, const InstPlan& ip, int block);
 // a filled descriptor for the lean kernel and this program
 void set_lean(sg::InstDesc& d, const std::vector<sg::SgOp>& lean);
 // Launch shape of a pass: sub-tiles per tile (clamped when values are staged for

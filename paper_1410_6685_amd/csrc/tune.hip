@@ -153,12 +153,12 @@ sg_status features(sg_program_s* P, const sg_plan* plan, const std::vector<sg_no
     f[22] = (float)bytes;
     int occ = 0;
     for (auto& ip : tmp.insts) {
-        // the same LDS rows as the execution: none for the accumulators of a specialized kernel
-        const bool spec = P->ctx->specialize;
-        const int ns = spec ? 0 : (int)ip.slot_kind.size(), nu = spec ? 0 : ip.nsum, ce = inst_cemit(ip);
+        // the same kernel and LDS rows as the execution (a specialized kernel counts as the general one)
+        const PassRows rows = pass_rows(P->ctx, ip, plan->block);
+        const int ns = rows.slots, nu = rows.sums, ce = inst_cemit(ip);
         const int C = stream_substeps(plan->substeps, plan->block, plan->unroll, ns, nu, ce, ip.scan_space != 0, 2);
         const size_t lds = stream_lds_bytes(ns, nu, ce, C, plan->block, plan->unroll, 2);
-        const int o = std::min(sg_stream_occupancy(plan->unroll, true, false, plan->block, lds), lds_blocks_per_cu(lds));
+        const int o = std::min(sg_stream_occupancy(plan->unroll, true, rows.lean, plan->block, lds), lds_blocks_per_cu(lds));
         occ = occ == 0 ? o : std::min(occ, o);
     }
     f[23] = (float)occ;  // resident blocks per CU of the tightest pass

@@ -150,6 +150,32 @@ def test_features_and_selector(sg, ctx):
     assert fb
 
 
+@pytest.mark.parametrize("plan", [(64, 1, 2, -1), (128, 2, 2, -1), (256, 1, 2, -1), (256, 2, 2, -1), (256, 4, 2, -1),
+                                  (512, 2, 2, -1), (1024, 4, 2, -1)])
+@pytest.mark.parametrize("chain", ["one value", "exp"])
+def test_occupancy_feature_is_the_launched_kernels(sg, plan, chain):
+    """The feature of resident blocks per CU describes the interpreter that the plan launches (the
+    lean one up to 256 threads for a chain with one running value): a pass over more tiles than
+    fit the device launches that many blocks per CU."""
+    import torch
+    c = sg.Context(0)
+    n = 1 << 26
+    x = torch.zeros(n, device="cuda")
+    a = c.wrap(x)
+    y = a.map(sg.Fn.affine(2.0, 1.0)) if chain == "one value" else a.map(sg.Fn.unary("exp"))
+    p = sg.Program(c)
+    p.add_root(y.reduce("sum"))
+    p.set_plan(plan)
+    say("occupancy", chain, plan)
+    p.execute()
+    grid, block, unroll = c.last_launch()[:3]
+    assert (block, unroll) == plan[:2]
+    per_cu = int(p.features(plan)[23])
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    tiles = n // (plan[0] * 4 * plan[1] * plan[2])
+    assert grid == min(tiles, per_cu * cus)
+
+
 def selector_inputs(spec, seed):
     out = {}
     for k, inp in enumerate(spec["inputs"]):
