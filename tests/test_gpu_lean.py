@@ -130,3 +130,41 @@ def test_a_finalizer_that_gives_up_is_reported(sg, n, specialize):
             c.set_wait_limit(-1)
         status, verdicts = built.program.execute()
         compare(spec, built, status, verdicts, want)
+
+
+@pytest.mark.parametrize("n", [1, 777, 37 * 8192, 37 * 8192 + 5001])
+@pytest.mark.parametrize("plan", [(256, 2, 4), (64, 1, 8), (128, 4, 2)])
+@pytest.mark.parametrize("batched", [False, True])
+def test_lean_and_general_interpreter_give_the_same_bits(sg, n, plan, batched):
+    """A chain with one running value runs on the lean kernel; with a maximum over exp(x) beside it
+    the same chain runs on the general one.  At one launch shape every float64 sum, element and
+    extremum has the same bits."""
+    import torch
+    c = sg.Context(0)
+    x, y = (torch.from_numpy(W.normal_f32(n, s)).cuda() for s in (21, 22))
+    say("lean and general", n, plan, batched)
+    got = []
+    for general in (False, True):
+        a, b = c.wrap(x), c.wrap(y)
+        z = a.map(sg.Fn.affine(1.5, -0.25)).zip(b, "mul")
+        k = z.filter(sg.Pred.cmp("gt", -0.5))
+        roots = [z.reduce("sum"), k.reduce("sum"), k.reduce("max"), z.reduce("min")]
+        p = sg.Program(c)
+        for r in roots:
+            p.add_root(r)
+        if not batched:
+            p.add_root(z)
+        if general:
+            p.add_root(a.map(sg.Fn.unary("exp")).reduce("max"))
+        if batched:
+            c.set_launch(*plan[:2])
+            c.set_batch_substeps(plan[2])
+            sg.Batch(c, [p], use_graph=False).run()
+        else:
+            p.set_plan(plan + (-1,))
+            assert p.features(plan + (-1,))[21] == 1
+            p.execute()
+            assert c.last_launch()[:4] == (min(c.last_launch()[0], -(-n // (plan[0] * 4 * plan[1] * plan[2]))),) + plan
+        bits = [np.array([r.shadow(), r.scalar()[0]]).view(np.uint64).tolist() for r in roots]
+        got.append((bits, z.to_host().view(np.uint32).tolist() if not batched else None, c.last_launch()[0]))
+    assert got[0] == got[1]
