@@ -433,8 +433,8 @@ typedef enum sg_plan_source { SG_PLAN_DEFAULT = 0, SG_PLAN_AUTOTUNE = 1, SG_PLAN
  * SG_E_STATE for a model without standardization. */
 sg_status sg_ctx_set_plan_source(sg_ctx ctx, int32_t source, const sg_plan* plans, int32_t n, int32_t reps,
                                  sg_mlp model, sg_tunedb db, float margin);
-/* The plan a program runs with (the context's settings where it has none) and how it was
- * chosen (an sg_plan_source value). */
+/* The plan a program runs with (the context's settings where it has none: short vectors then
+ * run on tiles of fewer sub-tiles) and how it was chosen (an sg_plan_source value). */
 sg_status sg_program_plan(sg_program p, sg_plan* plan, int32_t* source);
 
 /* Training data of the cost model, prepared on the device: fits the model's standardization

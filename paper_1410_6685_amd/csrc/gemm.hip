@@ -10,12 +10,12 @@
 // Matrices too small to give every CU a 128 x 128 tile run on 64 x 64 ones, and if those are
 // fewer than two per CU, K is cut into parts whose products are added in order by a second
 // kernel (the sums' rounding errors shrink with it).  Before (128 x 128 tiles only, guarded
-// loads on unaligned rows) and now: 1000 x 1531 x 777 181 and 45 us, 1024^3 87 and 34 us,
-// 64 x 4096 x 64 497 and 18 us, 4095 x 4095 x 4093 1629 and 1147 us, 4096^3 1060 and 986 us
-// (139 TFLOP/s of the matrix cores' 157 in FP32).
+// loads on unaligned rows) and now: 1000 x 1531 x 777 181 and 44 us, 1024^3 85 and 34 us,
+// 64 x 4096 x 64 497 and 20 us, 4095 x 4095 x 4093 1583 and 1005 us, 4096^3 1067 and 1005 us
+// (137 TFLOP/s of the matrix cores' 157 in FP32, which are busy 87 % of the cycles).
 //
 // The bfloat16 cores, on three parts per value, are no way round that bound.  With six of the
-// nine part products 4096^3 takes 706 us, but a single product is off by up to 1.4 units in the
+// nine part products 4096^3 takes 706 us (986 here, alone), but a single product is off by up to 1.4 units in the
 // last place (here 0.5; a diagonal or selecting factor shows it).  Eight, the small ones added up
 // apart, bring that to 0.51 and halve a dense sum's error, and then 2048^3 takes 161 us against
 // 159 here; a 256-wide tile no longer fits the registers.
